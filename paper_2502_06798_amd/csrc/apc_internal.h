@@ -45,13 +45,15 @@ hipError_t launch_quantize_rows(int dt, int64_t n, int32_t d, const float* x, vo
 __host__ __device__ inline int64_t factor_pad(int64_t n) { return (n + 255) / 256 * 256; }
 
 // ---- similarity + top-k ----------------------------------------------------
-enum { KERNEL_TILED = 0, KERNEL_STREAM_64 = 1, KERNEL_STREAM_32 = 2, KERNEL_QS = 4, KERNEL_QS8 = 5, KERNEL_F32S = 6 };
+enum { KERNEL_TILE = 0, KERNEL_QS = 1, KERNEL_QS8 = 2, KERNEL_F32S = 3 };
 struct MatchPlan {
     int kernel;        // kernel variant id
     int bq;            // queries per workgroup tile
     int qtiles;        // ceil(b / bq)
     int splits;        // workgroups along the entries per query tile
     int64_t b_pad;     // qtiles * bq
+    int chunk;         // tiled kernel: queries of one pass, whether splits share buckets
+    int buckets;
     size_t off_fq, off_gt, off_g2, off_ps, off_pi, off_qp, bytes;   // workspace layout
 };
 MatchPlan plan_match(int dt, int64_t n, int32_t d, int32_t b, int32_t k);
@@ -61,12 +63,6 @@ hipError_t launch_match(const MatchPlan& p, int dt, int64_t n, int32_t d, const 
                         const float* fe, const void* q, const float* q_scale, int32_t b, int32_t k,
                         float* top_score, int32_t* top_idx, void* ws, hipStream_t s,
                         hipEvent_t ev_start, hipEvent_t ev_stop);
-
-// streaming kernel for small batches (query factors are computed inside and
-// written to fq by the first split)
-hipError_t launch_stream(const MatchPlan& p, int dt, int64_t n, int32_t d, const void* emb,
-                         const float* fe, const void* q, const float* q_scale, int32_t b, int32_t k,
-                         float* fq, float* ps, int* pi, hipStream_t s);
 
 // query-stationary kernel for 16-bit and e4m3 rows of 512, 768, 1024 or 1536 bytes (k <= qs_max_k()):
 // queries in VGPRs, cache rows through an LDS ring, per-query bounds shared

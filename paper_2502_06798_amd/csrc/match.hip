@@ -1,0 +1,344 @@
+// Nearest cached prompts: cosine similarity of every query against every
+// cache entry, fused with an exact per-query top-k.
+//
+// The plan of a match (which kernel, its tiles and splits, the workspace), the
+// launches, and k_topk_merge: one wavefront per query merges the partial lists
+// of all splits (each sorted, ranges disjoint) by repeated wave argmax.
+//
+// Every score is produced by the same fixed sequence of MFMAs whatever the
+// tiling, and the final list is the unique top-k of those scores under a
+// total order, so results are deterministic.
+#include "apc_internal.h"
+#include "tile.h"
+
+namespace apc {
+namespace {
+
+constexpr int IDX_NONE = 0x7fffffff;
+
+__device__ inline float neg_inf() { return -__builtin_huge_valf(); }
+
+// (sa, ia) comes before (sb, ib) in the order score desc, index asc
+__device__ inline bool before(float sa, int ia, float sb, int ib)
+{
+    return sa > sb || (sa == sb && ia < ib);
+}
+
+// ---- merge of the per-split partial lists ----------------------------------
+// (score, index) as one key ordered like (score desc, index asc): the score's
+// bits mapped to an order-preserving unsigned integer, then the complement of
+// the index.  Adding +0 turns -0 into +0, which compare equal as scores.
+__device__ inline uint64_t merge_key(float s, int i)
+{
+    const uint32_t u = __float_as_uint(s + 0.0f);
+    const uint32_t o = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    return ((uint64_t)o << 32) | (uint32_t)~(uint32_t)i;
+}
+__device__ inline float merge_key_score(uint64_t key)
+{
+    const uint32_t o = (uint32_t)(key >> 32);
+    return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
+}
+// one step of a wavefront maximum: the key of the lane that the DPP control
+// names (own key where it names none, or the row is masked off)
+template <int CTRL, int ROWS>
+__device__ inline uint64_t dpp_max_step(uint64_t v)
+{
+    const int lo = (int)(uint32_t)v, hi = (int)(uint32_t)(v >> 32);
+    const uint32_t olo = (uint32_t)__builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xf, false);
+    const uint32_t ohi = (uint32_t)__builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xf, false);
+    const uint64_t o = ((uint64_t)ohi << 32) | olo;
+    return o > v ? o : v;
+}
+// largest key of the wavefront, in every lane: quads (xor 1, xor 2), half
+// rows (mirror), rows (mirror), then rows 1 and 3 take row 0's and row 2's
+// maximum (broadcast of lane 15) and rows 2 and 3 row 1's (lane 31): lane 63
+// ends with the maximum of all 64 lanes
+__device__ inline uint64_t wave_max_key(uint64_t v)
+{
+    v = dpp_max_step<0xB1, 0xf>(v);      // quad_perm [1, 0, 3, 2]
+    v = dpp_max_step<0x4E, 0xf>(v);      // quad_perm [2, 3, 0, 1]
+    v = dpp_max_step<0x141, 0xf>(v);     // row_half_mirror
+    v = dpp_max_step<0x140, 0xf>(v);     // row_mirror
+    v = dpp_max_step<0x142, 0xa>(v);     // row_bcast:15
+    v = dpp_max_step<0x143, 0xc>(v);     // row_bcast:31
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), 63);
+    return ((uint64_t)hi << 32) | lo;
+}
+
+template <int MAXOWN>
+__global__ __launch_bounds__(256) void k_topk_merge(const float* __restrict__ part_s,
+                                                     const int* __restrict__ part_i, int splits,
+                                                     int64_t b_pad, int32_t k, int32_t b,
+                                                     const float* __restrict__ fq,
+                                                     float* __restrict__ top_s, int32_t* __restrict__ top_i)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (q >= b) return;
+    const float f = fq[q];
+    if (!(f == f)) {                      // invalid query row
+        for (int p = lane; p < k; p += 64) {
+            top_s[q * k + p] = __int_as_float(0x7fc00000);
+            top_i[q * k + p] = -1;
+        }
+        return;
+    }
+    const int ne = splits * k;                                     // this query's entries
+    const float* gs = part_s + (int64_t)q * ne;
+    const int* gi = part_i + (int64_t)q * ne;
+    // a lane's list heads advance by loads from this query's block, which the
+    // first loads bring into the vector cache
+    auto fetch = [&](int l, int hd, float& sc, int& ix) {
+        sc = gs[l * k + hd];
+        ix = gi[l * k + hd];
+    };
+    int head[MAXOWN];
+    float cs[MAXOWN];
+    int ci[MAXOWN];
+#pragma unroll
+    for (int j = 0; j < MAXOWN; ++j) {
+        const int l = lane + 64 * j;
+        head[j] = 0;
+        if (l < splits) {
+            fetch(l, 0, cs[j], ci[j]);
+        } else {
+            cs[j] = neg_inf();
+            ci[j] = IDX_NONE;
+        }
+    }
+    for (int p = 0; p < k; ++p) {
+        float bs = cs[0];
+        int bi = ci[0], bj = 0;
+#pragma unroll
+        for (int j = 1; j < MAXOWN; ++j)
+            if (before(cs[j], ci[j], bs, bi)) { bs = cs[j]; bi = ci[j]; bj = j; }
+        const uint64_t wk = wave_max_key(merge_key(bs, bi));
+        const float ws = merge_key_score(wk);
+        const int wi = (int)~(uint32_t)wk;
+        if (lane == 0) {
+            top_s[q * k + p] = ws;
+            top_i[q * k + p] = wi == IDX_NONE ? -1 : wi;
+        }
+        if (wi != IDX_NONE && bi == wi) {          // entry indices are unique: one owner
+#pragma unroll
+            for (int j = 0; j < MAXOWN; ++j)
+                if (j == bj) {
+                    ++head[j];
+                    const int l = lane + 64 * j;
+                    if (head[j] < k) {
+                        fetch(l, head[j], cs[j], ci[j]);
+                    } else {
+                        cs[j] = neg_inf();
+                        ci[j] = IDX_NONE;
+                    }
+                }
+        }
+    }
+}
+
+inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+}  // namespace
+
+namespace {
+
+MatchPlan plan_tile(int dt, int64_t n, int64_t rb, int32_t b, int32_t k)
+{
+    MatchPlan p{};
+    p.kernel = KERNEL_TILE;
+    // queries of one pass: the logs stay below 26 MB, the copy of the queries
+    // below 6 MB unless 32 queries are longer
+    const int64_t copy = tile_stages(rb) * 64;
+    int64_t chunk = (6 << 20) / copy / 256 * 256;
+    if (chunk < 256) chunk = (6 << 20) / copy >= 128 ? 128 : (6 << 20) / copy >= 64 ? 64 : 32;
+    const int64_t most = k <= 32 ? 65536 : 32768;
+    if (chunk > most) chunk = most;
+    const int64_t bc = b < chunk ? b : chunk;
+    p.chunk = (int)chunk;
+    // The tile that takes the least time by this model: a workgroup goes
+    // through its tiles one after the other (one workgroup per CU), each
+    // stage of 64 bytes taking s us and each tile e us besides, as measured
+    // (float32 is bound by its MFMAs, the others by the loads and barriers of
+    // a stage).  256 queries pay where the batch fills them (512 x 250,000 x
+    // 1,024 f16: 315 us against 331 with 128); for other batches the padding and
+    // the uneven last round decide (600 x 100,000 x 640 f16: 146 us with 256,
+    // 124 with 128; 300 x 20,000 x 384 float32: 127 us with 256, 72 with 64).
+    static const struct { int bq; float s, s32, e; } kinds[4] = {
+        {256, 1.10f, 4.00f, 4.0f}, {128, 0.60f, 2.05f, 2.0f}, {64, 0.36f, 1.05f, 1.2f}, {32, 0.30f, 0.57f, 1.0f}};
+    const int64_t tiles = (n + 255) / 256, stages = tile_stages(rb);
+    float best = 0.f;
+    for (const auto& kd : kinds) {
+        if (kd.bq > 128 && k > 32) continue;                       // the logs of 256 queries would not fit
+        if (kd.bq > chunk) continue;
+        const int64_t qt = (bc + kd.bq - 1) / kd.bq;
+        int64_t sp = qt >= 256 ? 1 : 256 / qt;
+        if (sp > tiles) sp = tiles;                                // fewer rows than a tile's gain nothing
+        const int64_t passes = (qt * sp + 255) / 256;
+        const float rounds = dt == APC_F32 ? (float)tiles / sp : (float)((tiles + sp - 1) / sp);
+        const float t = passes * rounds * (stages * (dt == APC_F32 ? kd.s32 : kd.s) + kd.e);
+        if (best > 0.f && t >= best) continue;
+        best = t;
+        p.bq = kd.bq;
+        p.qtiles = (int)qt;
+        p.splits = (int)sp;
+    }
+    p.b_pad = (int64_t)p.qtiles * p.bq;
+    const size_t lists = (size_t)p.splits * p.b_pad;
+    p.off_fq = 0;
+    p.off_gt = align256(sizeof(float) * (size_t)p.b_pad);          // buckets
+    // (the buckets are used where every one of the k gets rows: see tile_kernel.h)
+    p.buckets = tile_classes(p.bq) * p.splits >= k;
+    p.off_g2 = align256(p.off_gt + (p.buckets ? sizeof(int) * (size_t)p.b_pad * k : 0));   // log lengths
+    p.off_ps = align256(p.off_g2 + sizeof(int) * lists);           // logs
+    p.off_qp = align256(p.off_ps + sizeof(uint64_t) * lists * tile_log_cap(k));
+    p.bytes = align256(p.off_qp + (size_t)(p.b_pad * copy));
+    // Never less than the workspace of lists of k pairs over 128-query tiles,
+    // 256 (k > 16) or 512 workgroups: callers with a workspace of a fixed size
+    // (apc_match_batch_static) are refused exactly the batches beyond that.
+    const size_t q128 = ((size_t)b + 127) / 128, n128 = ((size_t)n + 127) / 128;
+    size_t sp128 = ((k <= 16 ? 512 : 256) + q128 - 1) / q128;
+    sp128 = sp128 < n128 ? sp128 : n128;
+    const size_t least = 2 * align256(512 * q128) + 2 * align256(512 * q128 * sp128 * k);
+    if (p.bytes < least) p.bytes = least;
+    return p;
+}
+
+}  // namespace
+
+MatchPlan plan_match(int dt, int64_t n, int32_t d, int32_t b, int32_t k)
+{
+    MatchPlan p{};
+    const int64_t rb = (int64_t)d * elem_bytes(dt);
+    const int q2b = qs_queries(dt, rb, k);
+    const int q8b = qs8_queries(dt, rb, k);
+    if (q8b > 0 && b > 256) {
+        // large batches of 512- or 768-byte rows: two wavefronts per SIMD,
+        // 256 queries per workgroup, one workgroup per CU
+        p.kernel = KERNEL_QS8;
+        p.bq = q8b;
+        p.qtiles = (b + p.bq - 1) / p.bq;
+        const int64_t ngr = (n + qs8_group_rows() - 1) / qs8_group_rows();
+        int64_t splits = p.qtiles >= 256 ? 1 : 256 / p.qtiles;
+        if (splits > ngr) splits = ngr;
+        if (splits < 1) splits = 1;
+        p.splits = (int)splits;
+    } else if (q2b > 0 && k <= qs_max_k()) {
+        // 16-bit or e4m3 rows: queries in VGPRs, cache rows through LDS, one
+        // workgroup per CU; the query tiles of a split share an XCD
+        p.kernel = KERNEL_QS;
+        p.bq = q2b;
+        p.qtiles = (b + p.bq - 1) / p.bq;
+        if (p.qtiles < 1) p.qtiles = 1;
+        const int64_t gr = qs_group_rows(rb, k);
+        const int64_t ngr = (n + gr - 1) / gr;
+        int64_t splits = p.qtiles >= 256 ? 1 : 256 / p.qtiles;
+        if (splits > ngr) splits = ngr;
+        if (splits < 1) splits = 1;
+        p.splits = (int)splits;
+    } else if (f32s_fits(dt, n, d, b, k)) {
+        // small float32 caches: a workgroup per 32-row block, d over its wavefronts
+        p.kernel = KERNEL_F32S;
+        p.bq = f32s_queries();
+        p.qtiles = (b + p.bq - 1) / p.bq;
+        p.splits = (int)((n + f32s_rows() - 1) / f32s_rows());
+    } else {
+        return plan_tile(dt, n, rb, b, k);
+    }
+    p.b_pad = (int64_t)p.qtiles * p.bq;
+    p.off_fq = 0;
+    p.off_gt = align256(p.off_fq + sizeof(float) * (size_t)p.b_pad);
+    // the two-wavefront kernel's per-split quantile scores (splits x b_pad)
+    p.off_g2 = align256(p.off_gt + sizeof(int) * (size_t)p.b_pad);
+    const size_t g2_bytes = p.kernel == KERNEL_QS8 ? sizeof(int) * (size_t)p.splits * p.b_pad : 0;
+    p.off_ps = align256(p.off_g2 + g2_bytes);
+    p.off_pi = align256(p.off_ps + sizeof(float) * (size_t)p.splits * p.b_pad * k);
+    p.off_qp = align256(p.off_pi + sizeof(int) * (size_t)p.splits * p.b_pad * k);
+    const size_t qp_bytes =
+        p.kernel == KERNEL_QS || p.kernel == KERNEL_QS8 ? (size_t)p.b_pad * (size_t)d * elem_bytes(dt) : 0;
+    p.bytes = align256(p.off_qp + qp_bytes);
+    return p;
+}
+
+hipError_t launch_match(const MatchPlan& p, int dt, int64_t n, int32_t d, const void* emb,
+                        const float* fe, const void* q, const float* q_scale, int32_t b, int32_t k,
+                        float* top_score, int32_t* top_idx, void* ws, hipStream_t s,
+                        hipEvent_t ev_start, hipEvent_t ev_stop)
+{
+    uint8_t* w = static_cast<uint8_t*>(ws);
+    float* fq = reinterpret_cast<float*>(w + p.off_fq);
+    float* ps = reinterpret_cast<float*>(w + p.off_ps);
+    int* pi = reinterpret_cast<int*>(w + p.off_pi);
+    const int64_t row_bytes = (int64_t)d * elem_bytes(dt);
+
+    hipError_t e;
+    if (p.kernel == KERNEL_TILE) {
+        TileArgs a{};
+        a.emb = static_cast<const uint8_t*>(emb);
+        a.fe = fe;
+        a.n = n;
+        a.fe_len = factor_pad(n);
+        a.fq = fq;
+        a.bucket = reinterpret_cast<int*>(w + p.off_gt);
+        a.cnt = reinterpret_cast<int32_t*>(w + p.off_g2);
+        a.log = reinterpret_cast<uint64_t*>(w + p.off_ps);
+        a.b_pad = p.b_pad;
+        a.rb = (int32_t)row_bytes;
+        a.k = k;
+        a.nst = (int32_t)tile_stages(row_bytes);
+        a.qcopy = w + p.off_qp;
+        a.splits = p.splits;
+        a.qtiles = p.qtiles;
+        a.cap = tile_log_cap(k);
+        a.buckets = p.buckets;
+        const int32_t chunk = p.chunk;
+        for (int32_t q0 = 0; q0 < b; q0 += chunk) {
+            a.b = b - q0 < chunk ? b - q0 : chunk;
+            if ((e = launch_tile_prep(dt, static_cast<const uint8_t*>(q) + (int64_t)q0 * row_bytes,
+                                      q_scale ? q_scale + q0 : nullptr, a.b, row_bytes, p.bq, a, fq, w + p.off_qp, s)) !=
+                hipSuccess)
+                return e;
+            if (ev_start && q0 == 0 && (e = hipEventRecord(ev_start, s)) != hipSuccess) return e;
+            if ((e = launch_tile(dt, p.bq, a, s)) != hipSuccess) return e;
+            if (ev_stop && q0 + chunk >= b && (e = hipEventRecord(ev_stop, s)) != hipSuccess) return e;
+            if ((e = launch_tile_merge(a, top_score + (int64_t)q0 * k, top_idx + (int64_t)q0 * k, s)) != hipSuccess) return e;
+        }
+        return hipSuccess;
+    } else if (p.kernel == KERNEL_F32S) {
+        if ((e = launch_row_factors(dt, b, d, q, q_scale, nullptr, 0, fq, nullptr, s)) != hipSuccess) return e;
+        if (ev_start && (e = hipEventRecord(ev_start, s)) != hipSuccess) return e;
+        e = launch_f32s(p, n, d, emb, fe, q, fq, b, k, ps, pi, s);
+    } else if (p.kernel == KERNEL_QS) {
+        int* gt = reinterpret_cast<int*>(w + p.off_gt);
+        uint8_t* qp = w + p.off_qp;
+        if ((e = launch_qprep(dt, q, q_scale, b, p.b_pad, row_bytes, fq, gt, qp, p.bq, 4, nullptr, 0, s)) != hipSuccess)
+            return e;
+        if (ev_start && (e = hipEventRecord(ev_start, s)) != hipSuccess) return e;
+        e = launch_qs(p, dt, n, d, emb, fe, qp, fq, gt, b, k, ps, pi, s);
+    } else if (p.kernel == KERNEL_QS8) {
+        int* gt = reinterpret_cast<int*>(w + p.off_gt);
+        uint8_t* qp = w + p.off_qp;
+        int* g2 = reinterpret_cast<int*>(w + p.off_g2);
+        if ((e = launch_qprep(dt, q, q_scale, b, p.b_pad, row_bytes, fq, gt, qp, p.bq, 8, g2, p.splits, s)) != hipSuccess)
+            return e;
+        if (ev_start && (e = hipEventRecord(ev_start, s)) != hipSuccess) return e;
+        e = launch_qs8(p, dt, n, d, emb, fe, qp, fq, gt, g2, b, k, ps, pi, s);
+    } else {
+        return hipErrorInvalidValue;
+    }
+    if (e != hipSuccess) return e;
+    if (ev_stop && (e = hipEventRecord(ev_stop, s)) != hipSuccess) return e;
+    const dim3 grid((unsigned)((b + 3) / 4)), block(256);
+    if (p.splits <= 64)
+        k_topk_merge<1><<<grid, block, 0, s>>>(ps, pi, p.splits, p.b_pad, k, b, fq, top_score, top_idx);
+    else if (p.splits <= 128)
+        k_topk_merge<2><<<grid, block, 0, s>>>(ps, pi, p.splits, p.b_pad, k, b, fq, top_score, top_idx);
+    else if (p.splits <= 256)
+        k_topk_merge<4><<<grid, block, 0, s>>>(ps, pi, p.splits, p.b_pad, k, b, fq, top_score, top_idx);
+    else
+        k_topk_merge<8><<<grid, block, 0, s>>>(ps, pi, p.splits, p.b_pad, k, b, fq, top_score, top_idx);
+    return hipGetLastError();
+}
+
+}  // namespace apc

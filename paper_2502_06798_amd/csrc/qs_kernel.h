@@ -41,7 +41,7 @@
 
 #include <type_traits>
 
-#include "topk_wg.h"
+#include "qs_common.h"
 
 namespace apc {
 namespace {

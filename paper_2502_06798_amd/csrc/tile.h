@@ -1,0 +1,41 @@
+// Arguments and launches of the tiled similarity kernel (tile_kernel.h).
+#pragma once
+
+#include "apc_internal.h"
+
+namespace apc {
+
+struct TileArgs {
+    const uint8_t* emb;
+    const float* fe;
+    int64_t n;
+    int64_t fe_len;         // entry factors allocated (zeros past n)
+    const uint8_t* qcopy;   // the queries in the kernel's load order (tile_copy_bytes)
+    const float* fq;        // query factors (NaN: cannot be matched), b_pad
+    int* bucket;            // [k][b_pad] order-preserving keys of the shared maxima
+    uint64_t* log;          // [b_pad][splits][cap] keys
+    int32_t* cnt;           // [b_pad][splits]
+    int64_t b_pad;
+    int32_t b, rb, k, nst, splits, qtiles, cap, buckets;
+};
+
+hipError_t launch_tile_f32(int bq, const TileArgs& a, hipStream_t s);
+hipError_t launch_tile_f16(int bq, const TileArgs& a, hipStream_t s);
+hipError_t launch_tile_bf16(int bq, const TileArgs& a, hipStream_t s);
+hipError_t launch_tile_e4m3(int bq, const TileArgs& a, hipStream_t s);
+
+// query factors, reset buckets, and the copy of the queries: stage j (64 bytes
+// of d) of query tile t is the BQ x 64 bytes at (t nst + j) BQ 64, unit u of
+// row r at place u ^ (r / 4 % 4) of its 64 bytes; zeros past d and past b
+hipError_t launch_tile_prep(int dt, const void* q, const float* q_scale, int32_t b, int64_t row_bytes, int bq,
+                            const TileArgs& a, float* fq, uint8_t* qcopy, hipStream_t s);
+hipError_t launch_tile(int dt, int bq, const TileArgs& a, hipStream_t s);
+hipError_t launch_tile_merge(const TileArgs& a, float* top_s, int32_t* top_i, hipStream_t s);
+// stages of 64 bytes per row: an even number, at least four
+inline int64_t tile_stages(int64_t row_bytes) { return row_bytes > 256 ? (row_bytes + 127) / 128 * 2 : 4; }
+// classes of disjoint rows per workgroup whose running maxima go into the buckets
+inline int tile_classes(int bq) { return bq == 256 ? 4 : bq == 128 ? 8 : 16; }
+// places of a (query, split) log
+int tile_log_cap(int32_t k);
+
+}  // namespace apc

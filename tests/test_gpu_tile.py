@@ -1,0 +1,140 @@
+"""The tiled similarity kernel at the sizes where it can go wrong: every query
+tile (32, 64, 128, 256 queries), rows that end inside a stage of 64 bytes or a
+slot of 128, splits whose last tile is partial or a single row, k at the edges
+of its bounds and logs, batches of several passes, logs that overflow."""
+import pytest
+import torch
+
+from tests.gpu_check import say
+
+pytestmark = pytest.mark.gpu
+
+DT = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16, "e4m3": torch.float8_e4m3fn}
+
+
+@pytest.fixture(scope="module")
+def apc():
+    import paper_2502_06798_amd as apc
+    apc.load()
+    assert torch.cuda.is_available()
+    return apc
+
+
+def rows(n, d, dtype, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    x = torch.randn((n, d), device="cuda", generator=g)
+    x /= torch.linalg.vector_norm(x, dim=1, keepdim=True)
+    if dtype == "e4m3":
+        return (x * 300.0).clamp(-448.0, 448.0).to(DT[dtype]), torch.full((n,), 1 / 300.0, device="cuda")
+    return x.to(DT[dtype]), None
+
+
+def match(apc, e, es, q, qs, k):
+    c = apc.apc_build_cache(e, es)
+    b = q.shape[0]
+    ts = torch.empty((b, k), dtype=torch.float32, device="cuda")
+    ti = torch.empty((b, k), dtype=torch.int32, device="cuda")
+    ws = apc.workspace_tensor(c, b, k)
+    apc.apc_match_batch(c, q, qs, k, ts, ti, ws)
+    torch.cuda.synchronize()
+    s1, i1 = ts.clone(), ti.clone()
+    ws.random_(0, 256)                                   # nothing may depend on what the workspace held
+    apc.apc_match_batch(c, q, qs, k, ts, ti, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(ts, s1) and torch.equal(ti, i1), "a second pass differs"
+    c.close()
+    return ts.double(), ti.long()
+
+
+def check(e, q, k, ts, ti, tol):
+    """Scores of the returned entries and of the exact ranking, in float64;
+    entries equal wherever the exact scores are further apart than float32 sums
+    can be off (d products of magnitude at most 1: under 1e-5 here; e4m3 MFMAs
+    align 64 products before they add them: 1e-4)."""
+    q64 = q.double() / torch.linalg.vector_norm(q.double(), dim=1, keepdim=True)
+    e64 = e.double() / torch.linalg.vector_norm(e.double(), dim=1, keepdim=True)
+    s = q64 @ e64.T
+    best, idx = torch.sort(s, dim=1, descending=True, stable=True)
+    assert (ti >= 0).all() and all(len(set(r.tolist())) == k for r in ti)
+    assert (torch.gather(s, 1, ti) - ts).abs().max() <= tol and (best[:, :k] - ts).abs().max() <= tol
+    lone = torch.ones_like(ti, dtype=torch.bool)
+    gap = (best[:, :-1] - best[:, 1:]) > tol
+    lone[:, 1:] &= gap[:, : k - 1]
+    m = min(k, gap.shape[1])
+    lone[:, :m] &= gap[:, :m]
+    assert torch.equal(ti[lone], idx[:, :k][lone])
+
+
+@pytest.mark.parametrize("dtype,b,n,d,k", [
+    ("f16", 32, 257, 8, 1), ("f16", 33, 513, 40, 10), ("bf16", 64, 2048, 1024, 16), ("f16", 65, 4100, 640, 17),
+    ("bf16", 128, 3000, 200, 32), ("f16", 129, 2900, 1544, 33), ("f16", 700, 3333, 640, 10), ("f16", 2000, 9000, 72, 13),
+    ("f32", 1, 20000, 4, 1), ("f32", 300, 2500, 100, 10), ("f32", 31, 20001, 768, 48), ("f32", 513, 1000, 260, 64),
+    ("e4m3", 1, 300, 16, 5), ("e4m3", 100, 2000, 384, 10), ("e4m3", 257, 5000, 640, 20), ("e4m3", 600, 1025, 240, 40),
+    ("e4m3", 1500, 4000, 256, 9),
+])
+def test_tile_edges(apc, dtype, b, n, d, k):
+    say(f"tile {dtype} b={b} n={n} d={d} k={k}")
+    e, es = rows(n, d, dtype, n + d)
+    q, qs = rows(b, d, dtype, b + 7)
+    ts, ti = match(apc, e, es, q, qs, k)
+    check(e, q, k, ts, ti, {"f32": 1e-5, "e4m3": 1e-4}.get(dtype, 1e-5))
+
+
+@pytest.mark.parametrize("b", [60, 150])
+def test_tile_batches_of_several_passes(apc, b):
+    """Rows so wide that the copy of the queries takes several passes."""
+    d, n, k = 40000, 300, 5
+    say(f"tile passes b={b} d={d}")
+    e, _ = rows(n, d, "f32", 3)
+    q, _ = rows(b, d, "f32", 4)
+    ts, ti = match(apc, e, None, q, None, k)
+    check(e, q, k, ts, ti, 1e-5)
+
+
+@pytest.mark.parametrize("dtype,b,n,k", [("f16", 40, 6000, 10), ("f16", 300, 3000, 32), ("f32", 300, 5000, 64), ("e4m3", 130, 4000, 16)])
+def test_tile_logs_overflow(apc, dtype, b, n, k):
+    """Every row is nearer than all before it, so every pair passes the bounds:
+    the logs fill and are cut again and again."""
+    d = 640
+    say(f"tile overflow {dtype} b={b} n={n} k={k}")
+    a, _ = rows(1, d, "f32", 5)
+    z, _ = rows(1, d, "f32", 6)
+    t = torch.linspace(1.5, 0.01, n, device="cuda")[:, None]
+    e = a + t * z
+    e /= torch.linalg.vector_norm(e, dim=1, keepdim=True)
+    q = a.repeat(b, 1)
+    sc = [None, None]
+    if dtype == "e4m3":
+        e, q, sc = e * 300, q * 300, [torch.ones(n, device="cuda"), torch.ones(b, device="cuda")]
+    e, q = e.to(DT[dtype]).contiguous(), q.to(DT[dtype]).contiguous()
+    ts, ti = match(apc, e, sc[0], q, sc[1], k)
+    check(e, q, k, ts, ti, {"f32": 1e-5, "e4m3": 1e-4}.get(dtype, 1e-5))
+    assert torch.equal(ti, ti[:1].expand_as(ti)), "equal queries differ"
+
+
+def test_tile_equal_rows_take_lower_index(apc):
+    for n, k in ((5000, 16), (3000, 64)):
+        say(f"tile ties n={n} k={k}")
+        row, _ = rows(1, 640, "f16", 8)
+        q, _ = rows(70, 640, "f16", 9)
+        _, ti = match(apc, row.repeat(n, 1).contiguous(), None, q, None, k)
+        assert torch.equal(ti, torch.arange(k, device="cuda").expand(70, k))
+
+
+def test_tile_invalid_queries(apc):
+    e, _ = rows(3000, 640, "f16", 10)
+    q, _ = rows(140, 640, "f16", 11)
+    q[3] = 0
+    q[77, 5] = float("nan")
+    q[139, 639] = float("inf")
+    c = apc.apc_build_cache(e)
+    ts = torch.empty((140, 9), dtype=torch.float32, device="cuda")
+    ti = torch.empty((140, 9), dtype=torch.int32, device="cuda")
+    apc.apc_match_batch(c, q, None, 9, ts, ti, apc.workspace_tensor(c, 140, 9))
+    torch.cuda.synchronize()
+    bad = [3, 77, 139]
+    good = [i for i in range(140) if i not in bad]
+    assert (ti[bad] == -1).all() and torch.isnan(ts[bad]).all()
+    check(e, q[good], 9, ts[good].double(), ti[good].long(), 1e-5)
+    c.close()
