@@ -64,13 +64,12 @@ hipError_t launch_match(const MatchPlan& p, int dt, int64_t n, int32_t d, const 
                         float* top_score, int32_t* top_idx, void* ws, hipStream_t s,
                         hipEvent_t ev_start, hipEvent_t ev_stop);
 
-// query-stationary kernel for 16-bit and e4m3 rows of 512, 768, 1024 or 1536 bytes (k <= qs_max_k()):
-// queries in VGPRs, cache rows through an LDS ring, per-query bounds shared
-// between workgroups.  qs_queries gives the queries per workgroup (0: not built).
+// query-stationary kernel for 16-bit rows of 1536 bytes (k <= 10): queries in
+// VGPRs, cache rows through an LDS ring, per-query bounds shared between
+// workgroups.  qs_queries gives the queries per workgroup (0: not built),
+// qs_group_rows the entries per group (the unit a split is made of).
 int qs_queries(int dt, int64_t row_bytes, int k);
-int qs_max_k();
-// entries per group (the unit a split is made of) of the shape qs_queries describes
-int qs_group_rows(int64_t row_bytes, int k);
+int qs_group_rows();
 // query factors into fq and reset bounds gthr, for b_pad rows (rows >= b get NaN)
 // query factors and bound reset for the query-stationary kernels; qperm
 // (b_pad x row_bytes bytes) receives the queries in the order that kernel's
@@ -90,7 +89,7 @@ hipError_t launch_qs8(const MatchPlan& p, int dt, int64_t n, int32_t d, const vo
                       hipStream_t s);
 
 // float32 caches of at most 512 blocks of 32 rows, d a multiple of 64, k <= 32,
-// b <= 256: one workgroup per 32-row block and 16-query tile, four wavefronts
+// b <= 48: one workgroup per 32-row block and 16-query tile, four wavefronts
 // over d (f32small.hip); the query factors come first from launch_row_factors
 bool f32s_fits(int dt, int64_t n, int32_t d, int32_t b, int32_t k);
 int f32s_queries();

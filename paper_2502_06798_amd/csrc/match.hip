@@ -144,40 +144,67 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 namespace {
 
+// The workspace of a plan with one list of k pairs for every (query, split),
+// by shape: what apc_match_workspace has always asked at least, so that a
+// caller with a workspace of a fixed size (apc_match_batch_static) is refused
+// exactly the batches beyond it, whichever kernel serves them.
+size_t list_bytes(int dt, int64_t n, int64_t rb, int32_t b, int32_t k)
+{
+    const bool stationary = dt != APC_F32 && k <= 32 && (rb == 512 || rb == 768 || rb == 1024 || rb == 1536);
+    const bool eight = stationary && rb != 1536 && b > 256;
+    const bool small = dt == APC_F32 && rb % 256 == 0 && k <= 32 && n <= 16384 && b <= 256;
+    const bool wide = stationary && (eight || (rb != 1536 && k <= 16));
+    const int64_t bq = small ? 16 : wide ? 256 : 128;
+    const int64_t rows = small ? 32 : eight || (stationary && (wide || (rb == 1536 && k > 16))) ? 64 : 128;
+    const int64_t qt = (b + bq - 1) / bq, parts = (n + rows - 1) / rows;
+    const int64_t target = stationary || k > 16 ? 256 : 512;
+    int64_t splits = small ? parts : stationary ? (qt >= target ? 1 : target / qt) : (target + qt - 1) / qt;
+    if (splits > parts) splits = parts;
+    const size_t bp = (size_t)(qt * bq), lists = bp * (size_t)splits;
+    return 2 * align256(4 * bp) + align256(eight ? 4 * lists : 0) + 2 * align256(4 * lists * k) +
+           align256(stationary ? bp * (size_t)rb : 0);
+}
+
 MatchPlan plan_tile(int dt, int64_t n, int64_t rb, int32_t b, int32_t k)
 {
     MatchPlan p{};
     p.kernel = KERNEL_TILE;
     // queries of one pass: the logs stay below 26 MB, the copy of the queries
-    // below 6 MB unless 32 queries are longer
+    // below 5.8 MB unless 32 queries are longer
     const int64_t copy = tile_stages(rb) * 64;
-    int64_t chunk = (6 << 20) / copy / 256 * 256;
-    if (chunk < 256) chunk = (6 << 20) / copy >= 128 ? 128 : (6 << 20) / copy >= 64 ? 64 : 32;
-    const int64_t most = k <= 32 ? 65536 : 32768;
+    int64_t chunk = (11 << 19) / copy / 256 * 256;
+    if (chunk < 256) chunk = (11 << 19) / copy >= 128 ? 128 : (11 << 19) / copy >= 64 ? 64 : 32;
+    const int64_t most = k <= 16 ? 65536 : 32768;
     if (chunk > most) chunk = most;
+    // passes of equal size (a pass takes as long for a part of its queries)
+    const int64_t passes_b = ((int64_t)b + chunk - 1) / chunk, unit = chunk < 256 ? chunk : 256;
+    chunk = (((int64_t)b + passes_b - 1) / passes_b + unit - 1) / unit * unit;
     const int64_t bc = b < chunk ? b : chunk;
     p.chunk = (int)chunk;
     // The tile that takes the least time by this model: a workgroup goes
     // through its tiles one after the other (one workgroup per CU), each
-    // stage of 64 bytes taking s us and each tile e us besides, as measured
-    // (float32 is bound by its MFMAs, the others by the loads and barriers of
-    // a stage).  256 queries pay where the batch fills them (512 x 250,000 x
-    // 1,024 f16: 315 us against 331 with 128); for other batches the padding and
-    // the uneven last round decide (600 x 100,000 x 640 f16: 146 us with 256,
-    // 124 with 128; 300 x 20,000 x 384 float32: 127 us with 256, 72 with 64).
-    static const struct { int bq; float s, s32, e; } kinds[4] = {
-        {256, 1.10f, 4.00f, 4.0f}, {128, 0.60f, 2.05f, 2.0f}, {64, 0.36f, 1.05f, 1.2f}, {32, 0.30f, 0.57f, 1.0f}};
+    // stage of 64 bytes taking s us (float32, which its MFMAs bound: s32), each
+    // tile e us besides, and the first one f us, as measured.  256 queries pay
+    // where the batch fills them (512 x 250,000 x 1,024 f16: 307 us against 329
+    // with 128; 1,024 x 1,000,000 x 640: 1,346 against 1,477); for other batches
+    // the padding and the uneven last round decide (600 x 100,000 x 640 f16:
+    // 146 us with 256, 124 with 128; 256 x 100,000 x 768: 92 and 85; 300 x
+    // 20,000 x 384 float32: 127 us with 256, 72 with 64).
+    static const struct { int bq; float s, s32, e, f; } kinds[4] = {{256, 1.10f, 4.00f, 4.0f, 12.f},
+                                                                    {128, 0.60f, 2.05f, 2.0f, 6.f},
+                                                                    {64, 0.36f, 1.05f, 1.2f, 3.f},
+                                                                    {32, 0.30f, 0.57f, 1.0f, 2.f}};
     const int64_t tiles = (n + 255) / 256, stages = tile_stages(rb);
     float best = 0.f;
     for (const auto& kd : kinds) {
-        if (kd.bq > 128 && k > 32) continue;                       // the logs of 256 queries would not fit
+        if (kd.bq > 128 && k > 16) continue;                       // longer logs (tile_log_cap)
         if (kd.bq > chunk) continue;
         const int64_t qt = (bc + kd.bq - 1) / kd.bq;
         int64_t sp = qt >= 256 ? 1 : 256 / qt;
         if (sp > tiles) sp = tiles;                                // fewer rows than a tile's gain nothing
         const int64_t passes = (qt * sp + 255) / 256;
         const float rounds = dt == APC_F32 ? (float)tiles / sp : (float)((tiles + sp - 1) / sp);
-        const float t = passes * rounds * (stages * (dt == APC_F32 ? kd.s32 : kd.s) + kd.e);
+        const float t = passes * (rounds * (stages * (dt == APC_F32 ? kd.s32 : kd.s) + kd.e) + kd.f);
         if (best > 0.f && t >= best) continue;
         best = t;
         p.bq = kd.bq;
@@ -189,33 +216,32 @@ MatchPlan plan_tile(int dt, int64_t n, int64_t rb, int32_t b, int32_t k)
     p.off_fq = 0;
     p.off_gt = align256(sizeof(float) * (size_t)p.b_pad);          // buckets
     // (the buckets are used where every one of the k gets rows: see tile_kernel.h)
-    p.buckets = tile_classes(p.bq) * p.splits >= k;
+    p.buckets = TL_CLASSES * p.splits >= k;
     p.off_g2 = align256(p.off_gt + (p.buckets ? sizeof(int) * (size_t)p.b_pad * k : 0));   // log lengths
     p.off_ps = align256(p.off_g2 + sizeof(int) * lists);           // logs
     p.off_qp = align256(p.off_ps + sizeof(uint64_t) * lists * tile_log_cap(k));
     p.bytes = align256(p.off_qp + (size_t)(p.b_pad * copy));
-    // Never less than the workspace of lists of k pairs over 128-query tiles,
-    // 256 (k > 16) or 512 workgroups: callers with a workspace of a fixed size
-    // (apc_match_batch_static) are refused exactly the batches beyond that.
-    const size_t q128 = ((size_t)b + 127) / 128, n128 = ((size_t)n + 127) / 128;
-    size_t sp128 = ((k <= 16 ? 512 : 256) + q128 - 1) / q128;
-    sp128 = sp128 < n128 ? sp128 : n128;
-    const size_t least = 2 * align256(512 * q128) + 2 * align256(512 * q128 * sp128 * k);
-    if (p.bytes < least) p.bytes = least;
     return p;
 }
 
-}  // namespace
-
-MatchPlan plan_match(int dt, int64_t n, int32_t d, int32_t b, int32_t k)
+MatchPlan plan_kernel(int dt, int64_t n, int32_t d, int32_t b, int32_t k)
 {
     MatchPlan p{};
     const int64_t rb = (int64_t)d * elem_bytes(dt);
     const int q2b = qs_queries(dt, rb, k);
     const int q8b = qs8_queries(dt, rb, k);
-    if (q8b > 0 && b > 256) {
-        // large batches of 512- or 768-byte rows: two wavefronts per SIMD,
-        // 256 queries per workgroup, one workgroup per CU
+    // Two wavefronts per SIMD with the queries in registers (no query loads at
+    // all), where there are many queries and its lists, slow to fill, have
+    // rows enough to pay: it reads the cache once per 256 queries from the L2,
+    // while the tiled kernel also streams the queries.  Measured, this one
+    // against the tiled one: 16,384 x 300,000 x 768 e4m3 3.39 and 4.20 ms,
+    // 16,384 x 30,000 (k = 32) 0.87 and 1.31, 4,096 x 1,000,000 x 512 f16 4.28
+    // and 4.68, 8,192 x 300,000 x 512 f16 2.68 and 2.76, 6,000 x 40,000 x 768
+    // e4m3 (k = 32) 0.57 and 0.64; but 2,048 x 1,000,000 x 768 e4m3 (k = 32) 2.14
+    // and 1.99, 3,000 x 300,000 x 256 f16 0.70 and 0.57, 8,192 x 20,000 x 512
+    // f16 0.33 and 0.28, 512 x 1,000,000 x 768 e4m3 (k = 32) 0.84 and 0.56.
+    const bool many = b >= 12288 ? n > 20000 : b >= 4096 && ((int64_t)b * n >= 2400000000ll || (k > 16 && n > 20000));
+    if (q8b > 0 && many) {
         p.kernel = KERNEL_QS8;
         p.bq = q8b;
         p.qtiles = (b + p.bq - 1) / p.bq;
@@ -224,21 +250,28 @@ MatchPlan plan_match(int dt, int64_t n, int32_t d, int32_t b, int32_t k)
         if (splits > ngr) splits = ngr;
         if (splits < 1) splits = 1;
         p.splits = (int)splits;
-    } else if (q2b > 0 && k <= qs_max_k()) {
-        // 16-bit or e4m3 rows: queries in VGPRs, cache rows through LDS, one
-        // workgroup per CU; the query tiles of a split share an XCD
+    } else if (q2b > 0 && ((b >= 128 && b <= 256 && n >= 65536 && n < 1000000) || (b <= 16 && n >= 500000))) {
+        // 16-bit rows of 1536 bytes, k <= 10: queries in VGPRs, cache rows through
+        // LDS, one workgroup per CU; the query tiles of a split share an XCD.
+        // For one or two tiles of 128 queries, and for the fewest queries against
+        // a large cache, it is still ahead of the tiled kernel (256 x 100,000: 76
+        // us and 85; 200 x 200,000: 114 and 128; 128 x 100,000: 63 and 67; 1 x
+        // 1,000,000: 270 and 276; 4 x 1,000,000: 275 and 278), elsewhere it is not
+        // (32 x 1,000,000: 289 and 286; 100 x 100,000: 60 and 57; 256 x 1,000,000:
+        // 504 and 497; 1,024 x 1,000,000: 1,660 and 1,490)
         p.kernel = KERNEL_QS;
         p.bq = q2b;
         p.qtiles = (b + p.bq - 1) / p.bq;
         if (p.qtiles < 1) p.qtiles = 1;
-        const int64_t gr = qs_group_rows(rb, k);
+        const int64_t gr = qs_group_rows();
         const int64_t ngr = (n + gr - 1) / gr;
         int64_t splits = p.qtiles >= 256 ? 1 : 256 / p.qtiles;
         if (splits > ngr) splits = ngr;
         if (splits < 1) splits = 1;
         p.splits = (int)splits;
     } else if (f32s_fits(dt, n, d, b, k)) {
-        // small float32 caches: a workgroup per 32-row block, d over its wavefronts
+        // small float32 caches and few queries: a workgroup per 32-row block, d
+        // over its wavefronts
         p.kernel = KERNEL_F32S;
         p.bq = f32s_queries();
         p.qtiles = (b + p.bq - 1) / p.bq;
@@ -258,6 +291,16 @@ MatchPlan plan_match(int dt, int64_t n, int32_t d, int32_t b, int32_t k)
     const size_t qp_bytes =
         p.kernel == KERNEL_QS || p.kernel == KERNEL_QS8 ? (size_t)p.b_pad * (size_t)d * elem_bytes(dt) : 0;
     p.bytes = align256(p.off_qp + qp_bytes);
+    return p;
+}
+
+}  // namespace
+
+MatchPlan plan_match(int dt, int64_t n, int32_t d, int32_t b, int32_t k)
+{
+    MatchPlan p = plan_kernel(dt, n, d, b, k);
+    const size_t least = list_bytes(dt, n, (int64_t)d * elem_bytes(dt), b, k);
+    if (p.bytes < least) p.bytes = least;
     return p;
 }
 
@@ -292,6 +335,10 @@ hipError_t launch_match(const MatchPlan& p, int dt, int64_t n, int32_t d, const 
         a.qtiles = p.qtiles;
         a.cap = tile_log_cap(k);
         a.buckets = p.buckets;
+        // query tiles that share an L2 (4 MB): about half of it
+        const int64_t fit = (2 << 20) / ((int64_t)a.nst * 64 * p.bq);
+        a.group = fit < 2 ? 2 : fit > 32 ? 32 : (int32_t)fit;
+        if (a.group > p.qtiles) a.group = p.qtiles;
         const int32_t chunk = p.chunk;
         for (int32_t q0 = 0; q0 < b; q0 += chunk) {
             a.b = b - q0 < chunk ? b - q0 : chunk;

@@ -1,4 +1,4 @@
-// Query-stationary similarity + exact top-k for 16-bit and e4m3 rows.
+// Query-stationary similarity + exact top-k for 16-bit rows.
 //
 // Grid: splits x query tiles.  A workgroup of four wavefronts (one per SIMD)
 // owns a tile of 4 x MQ x 32 queries and a contiguous range of cache entries
@@ -18,9 +18,8 @@
 //
 // Top-k, per wavefront (its queries are its own, so no cross-wave sync).
 // The two lanes of a query see disjoint entries; each keeps its own list of
-// the best pairs it has seen, as order-preserving 64-bit keys: in registers,
-// sorted, holding the KR best (LDS lists, unsorted, for 1024-byte rows with
-// two query blocks).  After each group of EB x 32 entries:
+// the best pairs it has seen, as order-preserving 64-bit keys in registers,
+// sorted, holding the KR best.  After each group of EB x 32 entries:
 //  * a lane's best score in the group is computed exactly (largest product
 //    times entry factor, times f_q, clamped: both steps are monotone), and
 //    only if it reaches the filter threshold does the lane look further;
@@ -52,7 +51,6 @@ constexpr int Q2_NW = 4;                   // wavefronts per workgroup
 constexpr int Q2_NT = Q2_NW * 64;
 constexpr int Q2_SB = 256;                 // bytes of each row per stage
 constexpr int Q2_FR = 8;                   // ring of per-group side data
-constexpr int Q2_KMAX = 32;                // largest k
 constexpr int Q2_LDS = 160 * 1024;         // LDS of a CU
 // s_waitcnt immediate: at most n vector-memory operations outstanding
 constexpr int Q2_PAIR_GROUPS = 8;          // groups of a split that bound the pair from both lists
@@ -127,11 +125,8 @@ struct Q2Cfg {
     static constexpr int GR = EB * 32;                // rows per stage and per group (EB blocks of 32)
     static constexpr int STAGE = GR * Q2_SB;          // bytes of a stage
     static constexpr int LPW = STAGE / 1024 / Q2_NW;  // row loads per wavefront per stage
-    static constexpr bool LREG = MQ == 1 || RB < 1024; // lists in registers (else LDS)
-    static constexpr bool LLDS = !LREG;               // lists in LDS
-    static constexpr int LIST_BYTES = LLDS ? Q2_NW * MQ * KR * 64 * 8 : 0;
     static constexpr int SIDE_BYTES = Q2_FR * GR * 4 + Q2_FR * Q2_NW * BQW * 4;
-    static constexpr int NS = (Q2_LDS - LIST_BYTES - SIDE_BYTES) / STAGE;   // stages in the LDS ring
+    static constexpr int NS = (Q2_LDS - SIDE_BYTES) / STAGE;   // stages in the LDS ring
     static_assert(NS >= 4, "LDS ring too small");
     static_assert(EB == 2 || EB == 4, "two or four blocks per group");
     static_assert(RB % Q2_SB == 0 && SPG >= 2, "rows must be at least two whole stages");
@@ -165,7 +160,6 @@ struct Q2Cfg {
         uint8_t e[NS * STAGE];
         float fe[Q2_FR][GR];                    // entry factors of a group
         int gthr[Q2_FR][Q2_NW][BQW];            // global bounds (keys) seen at a group start
-        uint64_t lst[LLDS ? Q2_NW : 1][MQ][LLDS ? KR : 1][64];   // per-lane lists of keys (LDS form), slot-major
     };
 };
 
@@ -202,31 +196,7 @@ __device__ inline float q2_key_score(uint64_t key)
 }
 __device__ inline int q2_key_entry(uint64_t key) { return key == 0 ? IDX_NONE : (int)~(uint32_t)key; }
 
-// smallest key of a lane's list (slots past k hold ~0 and are never the smallest):
-// all KR slots are read at once, then a tree of comparisons
-template <int KR>
-__device__ inline void q2_worst(const uint64_t* col, uint64_t& wkey, int& wp)
-{
-    uint64_t x[KR];
-    int xp[KR];
-#pragma unroll
-    for (int p = 0; p < KR; ++p) {
-        x[p] = col[p * 64];
-        xp[p] = p;
-    }
-#pragma unroll
-    for (int w = 1; w < KR; w *= 2)
-#pragma unroll
-        for (int p = 0; p + w < KR; p += 2 * w) {
-            const bool tk = x[p + w] < x[p];
-            x[p] = tk ? x[p + w] : x[p];
-            xp[p] = tk ? xp[p + w] : xp[p];
-        }
-    wkey = x[0];
-    wp = xp[0];
-}
-
-// register form, kept sorted by key descending: insert key (0 inserts
+// a list in registers, kept sorted by key descending: insert key (0 inserts
 // nothing), dropping the smallest.  Every slot compares once; a slot takes the
 // one before it when the key goes above that one, the key when it goes above
 // only this one.  Slots are written from the last up, so each new value can
@@ -442,30 +412,17 @@ __global__ __launch_bounds__(Q2_NT) void k_qs(
         for (int mq = 0; mq < MQ; ++mq) q2_use(qv[s2][mq]);
 #pragma unroll
     for (int mq = 0; mq < MQ; ++mq) asm volatile("" ::"v"(fq[mq]));
-    // per-lane lists.  Registers: the KR best keys, sorted descending (key 0:
-    // empty).  LDS: slots below k start empty, slots from k on hold ~0 so that
-    // they are never the worst.
-    constexpr bool LREG = C::LREG;
-    uint64_t* lcol[MQ];
-    uint64_t lk[LREG ? MQ : 1][KR];
+    // per-lane lists: the KR best keys, sorted descending (key 0: empty)
+    uint64_t lk[MQ][KR];
 #pragma unroll
-    for (int mq = 0; mq < MQ; ++mq) {
-        if constexpr (LREG) {
+    for (int mq = 0; mq < MQ; ++mq)
 #pragma unroll
-            for (int p = 0; p < KR; ++p) lk[mq][p] = 0ull;
-        } else {
-            lcol[mq] = &sm.lst[wave][mq][0][lane];
-#pragma unroll
-            for (int p = 0; p < KR; ++p) lcol[mq][p * 64] = p < k ? 0ull : ~0ull;
-        }
-    }
+        for (int p = 0; p < KR; ++p) lk[mq][p] = 0ull;
     uint64_t wkey[MQ];   // the lane's k-th key (0 while it has fewer than k)
-    int wp[MQ];          // its slot (lists in LDS)
     float ps[MQ];        // a lower bound on the query's k-th best from the pair's lists (-inf until known)
 #pragma unroll
     for (int mq = 0; mq < MQ; ++mq) {
         wkey[mq] = 0;
-        wp[mq] = 0;
         ps[mq] = neg_inf();
     }
 
@@ -731,14 +688,9 @@ __global__ __launch_bounds__(Q2_NT) void k_qs(
                     const int r = bsel & 15;
                     const int e = (int)(e0 + 32 * (bsel >> 4) + 8 * (r >> 2) + 4 * h + (r & 3));
                     const uint64_t key = q2_pack(sc, e);
-                    if constexpr (LREG) {
-                        q2_insert_sorted<KR>(lk[mq], act ? key : 0ull);
-                    } else if (act && key > wkey[mq]) {
-                        lcol[mq][wp[mq] * 64] = key;
-                        q2_worst<KR>(lcol[mq], wkey[mq], wp[mq]);
-                    }
+                    q2_insert_sorted<KR>(lk[mq], act ? key : 0ull);
                 }
-                if constexpr (LREG) wkey[mq] = q2_slot<KR>(lk[mq], k - 1);
+                wkey[mq] = q2_slot<KR>(lk[mq], k - 1);
             }
         }
         // The pair's bound for the next group, and the global bound.  Besides
@@ -751,7 +703,7 @@ __global__ __launch_bounds__(Q2_NT) void k_qs(
         for (int mq = 0; mq < MQ; ++mq) {
             const float own = q2_key_score(wkey[mq]);
             float pair = __builtin_fmaxf(own, __shfl_xor(own, 32, 64));
-            if constexpr (LREG) {
+            {
                 if (k >= 2 && gi < Q2_PAIR_GROUPS) {               // uniform
                     const int m1 = (k + 1) / 2, m2 = k - m1;
                     const uint64_t a = q2_slot<KR>(lk[mq], m1 - 1), c = q2_slot<KR>(lk[mq], m2 - 1);
@@ -779,28 +731,9 @@ __global__ __launch_bounds__(Q2_NT) void k_qs(
 #pragma unroll
         for (int p = 0; p < KP; ++p) {
             uint64_t v = 0ull;
-            if (p < KR) {
-                if constexpr (LREG) v = lk[mq][p];
-                else v = lcol[mq][p * 64];
-            }
-            x[p] = v == ~0ull ? 0ull : v;
+            if (p < KR) v = lk[mq][p];
+            x[p] = v;
         }
-        // bitonic sort, descending (register lists are sorted already)
-#pragma unroll
-        for (int size = 2; size <= (LREG ? 1 : KP); size *= 2)
-#pragma unroll
-            for (int stride = size / 2; stride > 0; stride /= 2)
-#pragma unroll
-                for (int i = 0; i < KP; ++i) {
-                    const int j = i ^ stride;
-                    if (j > i) {
-                        const bool desc = (i & size) == 0;
-                        const bool sw = desc ? x[i] < x[j] : x[i] > x[j];
-                        const uint64_t a0 = x[i], a1 = x[j];
-                        x[i] = sw ? a1 : a0;
-                        x[j] = sw ? a0 : a1;
-                    }
-                }
         // the larger of own[p] and partner[KP - 1 - p] is a bitonic sequence
         // holding the KP largest of both lists; half-cleaners sort it
         uint64_t m[KP];
@@ -848,62 +781,21 @@ hipError_t run_qs(const MatchPlan& p, int64_t n, const void* emb, const float* f
 
 }  // namespace
 
-// shape of the query-stationary kernel: rows of 512, 768, 1024 or 1536 bytes,
-// k <= 32.  Lists of 10 slots for k <= 10, 16 for k <= 16 (two query blocks
-// per wavefront except for 1536-byte rows), 32 otherwise (one query block).
-// Every insertion touches every slot, so the list is kept close to k.
-constexpr int q2_kr(int k) { return k <= 10 ? 10 : k <= 16 ? 16 : 32; }
-constexpr int q2_mq(int64_t row_bytes, int k) { return k <= 16 && row_bytes != 1536 ? 2 : 1; }
-// 32-row blocks per stage and group: four with one query block (two where
-// 1536-byte rows and 32-slot lists leave too few registers), two with two
-constexpr int q2_eb(int64_t row_bytes, int k)
-{
-    return q2_mq(row_bytes, k) == 2 || (row_bytes == 1536 && k > 16) ? 2 : 4;
-}
-constexpr int q2_rows(int64_t row_bytes, int k) { return 32 * q2_eb(row_bytes, k); }
-constexpr bool q2_built(int64_t row_bytes, int k)
-{
-    return (row_bytes == 512 || row_bytes == 768 || row_bytes == 1024 || row_bytes == 1536) && k >= 1 &&
-           k <= Q2_KMAX;
-}
-constexpr int q2_queries(int64_t row_bytes, int k) { return q2_built(row_bytes, k) ? Q2_NW * 32 * q2_mq(row_bytes, k) : 0; }
+// The shape that is built: 16-bit rows of 1536 bytes, one block of 32 queries
+// per wavefront, lists of 10 slots, four 32-row blocks per stage and group.
+constexpr int Q2_RB = 1536, Q2_KR = 10, Q2_EB = 4;
+constexpr int q2_queries(int64_t row_bytes, int k) { return row_bytes == Q2_RB && k >= 1 && k <= Q2_KR ? Q2_NW * 32 : 0; }
 
 template <int DT>
 hipError_t q2_dispatch(const MatchPlan& p, int64_t n, int64_t rb, const void* emb, const float* fe, const void* q,
                        const float* fq, int* gthr, int32_t b, int32_t k, float* ps, int* pi, hipStream_t s)
 {
-#define APC_Q2(RB, MQ, KR) run_qs<DT, RB, MQ, KR, q2_eb(RB, KR)>(p, n, emb, fe, q, fq, gthr, b, k, ps, pi, s)
-    if (q2_kr(k) == 10) {
-        switch (rb) {
-        case 1536: return APC_Q2(1536, 1, 10);
-        case 1024: return APC_Q2(1024, 2, 10);
-        case 768: return APC_Q2(768, 2, 10);
-        case 512: return APC_Q2(512, 2, 10);
-        }
-    } else if (q2_kr(k) == 16) {
-        switch (rb) {
-        case 1536: return APC_Q2(1536, 1, 16);
-        case 1024: return APC_Q2(1024, 2, 16);
-        case 768: return APC_Q2(768, 2, 16);
-        case 512: return APC_Q2(512, 2, 16);
-        }
-    } else {
-        switch (rb) {
-        case 1536: return APC_Q2(1536, 1, 32);
-        case 1024: return APC_Q2(1024, 1, 32);
-        case 768: return APC_Q2(768, 1, 32);
-        case 512: return APC_Q2(512, 1, 32);
-        }
-    }
-#undef APC_Q2
-    return hipErrorInvalidValue;
+    if (rb != Q2_RB || k > Q2_KR) return hipErrorInvalidValue;
+    return run_qs<DT, Q2_RB, 1, Q2_KR, Q2_EB>(p, n, emb, fe, q, fq, gthr, b, k, ps, pi, s);
 }
 
 hipError_t launch_qs_f16(const MatchPlan& p, int64_t n, int64_t rb, const void* emb, const float* fe, const void* q,
                          const float* fq, int* gthr, int32_t b, int32_t k, float* ps, int* pi, hipStream_t s);
 hipError_t launch_qs_bf16(const MatchPlan& p, int64_t n, int64_t rb, const void* emb, const float* fe, const void* q,
                           const float* fq, int* gthr, int32_t b, int32_t k, float* ps, int* pi, hipStream_t s);
-hipError_t launch_qs_e4m3(const MatchPlan& p, int64_t n, int64_t rb, const void* emb, const float* fe, const void* q,
-                          const float* fq, int* gthr, int32_t b, int32_t k, float* ps, int* pi, hipStream_t s);
-
 }  // namespace apc

@@ -16,7 +16,7 @@ struct TileArgs {
     uint64_t* log;          // [b_pad][splits][cap] keys
     int32_t* cnt;           // [b_pad][splits]
     int64_t b_pad;
-    int32_t b, rb, k, nst, splits, qtiles, cap, buckets;
+    int32_t b, rb, k, nst, splits, qtiles, cap, buckets, group;
 };
 
 hipError_t launch_tile_f32(int bq, const TileArgs& a, hipStream_t s);
@@ -33,8 +33,9 @@ hipError_t launch_tile(int dt, int bq, const TileArgs& a, hipStream_t s);
 hipError_t launch_tile_merge(const TileArgs& a, float* top_s, int32_t* top_i, hipStream_t s);
 // stages of 64 bytes per row: an even number, at least four
 inline int64_t tile_stages(int64_t row_bytes) { return row_bytes > 256 ? (row_bytes + 127) / 128 * 2 : 4; }
-// classes of disjoint rows per workgroup whose running maxima go into the buckets
-inline int tile_classes(int bq) { return bq == 256 ? 4 : bq == 128 ? 8 : 16; }
+// classes of disjoint rows per split whose running maxima go into the buckets:
+// the two lane halves of each of a tile's eight 32-row blocks
+constexpr int TL_CLASSES = 16;
 // places of a (query, split) log
 int tile_log_cap(int32_t k);
 

@@ -161,7 +161,11 @@ __global__ __launch_bounds__(TM_NT) void k_tile_merge(const uint64_t* __restrict
 
 }  // namespace
 
-int tile_log_cap(int32_t k) { return k <= 32 ? 48 : 96; }
+// A split's first tile logs about 12 pairs for k = 10, 21 for 16, 41 for 32
+// and 75 for 48; a log that fills costs its workgroup a pass over all its logs
+// (tens of us).  256 workgroups of 256 queries with logs of 48, or of 128 with
+// 96, take 25 MB.
+int tile_log_cap(int32_t k) { return k <= 16 ? 48 : 96; }
 
 hipError_t launch_tile_prep(int dt, const void* q, const float* q_scale, int32_t b, int64_t row_bytes, int bq,
                             const TileArgs& a, float* fq, uint8_t* qcopy, hipStream_t s)

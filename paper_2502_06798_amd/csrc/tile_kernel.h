@@ -24,7 +24,7 @@
 // places, the stores wait for nothing.  F comes from three places:
 //  * a split's first tile: its rows fall into 32 or 64 disjoint groups per
 //    query, and a value that k groups' maxima reach has k pairs at or above it;
-//  * all splits together: the lanes' running maxima (of disjoint rows, 2 WE
+//  * all splits together: the lanes' running maxima (of disjoint rows, 16
 //    classes per workgroup) go into k buckets per query by atomic max, after
 //    tiles 1, 2, 4, 8, ..; the smallest bucket has k pairs at or above it.
 //    It is read during the next tile.  After the first tiles this is close to the
@@ -71,7 +71,6 @@ struct TlCfg {
     static constexpr int QWB = QSLOT / TL_NW;                 // bytes of queries a wavefront loads per stage
     static constexpr int QLD = QWB >= 1024 ? QWB / 1024 : 1;  // in loads of 1 KB (or one of fewer lanes)
     static constexpr int OPS = ELD + QLD;
-    static constexpr int CLS = 2 * WE;                        // classes of disjoint rows with a running maximum each
     struct Smem {
         uint8_t e[NE * TL_ESLOT];
         uint8_t q[NQ * QSLOT];
@@ -161,13 +160,17 @@ __global__ __launch_bounds__(TL_NT) void k_tile(const TileArgs A)
     const int64_t n = A.n;
     const int rb = A.rb, k = A.k, splits = A.splits, nst = A.nst, cap = A.cap;
 
-    // workgroup id -> (split, query tile): the query tiles of a split get
-    // consecutive ids on one XCD and share its L2 (workgroups are dealt
-    // round-robin over the 8 XCDs)
+    // workgroup id -> (split, query tile).  Workgroups are dealt round-robin
+    // over the 8 XCDs; consecutive ids lin share one, and with it an L2.  They
+    // run over the query tiles of a group first, which read the same rows, then
+    // over the splits, which read the same queries, then over the groups: a
+    // group's queries (A.group tiles) stay in the L2.
     const int grid = (int)gridDim.x, work = splits * A.qtiles;
     const int lin = (grid & 7) == 0 ? (int)(blockIdx.x & 7) * (grid >> 3) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
     if (lin >= work) return;                                       // whole workgroup: uniform
-    const int split = lin / A.qtiles, qtile = lin % A.qtiles;
+    const int gi = lin / (A.group * splits), gl = lin - gi * A.group * splits;
+    const int gsize = A.qtiles - gi * A.group < A.group ? A.qtiles - gi * A.group : A.group;
+    const int split = gl / gsize, qtile = gi * A.group + gl % gsize;
     const int64_t q0 = (int64_t)qtile * BQ;
 
     // the split's rows: whole blocks of 32, so that splits differ by one block
@@ -246,10 +249,16 @@ __global__ __launch_bounds__(TL_NT) void k_tile(const TileArgs A)
         sm.cnt[i] = 0;
     }
     if (tid == 0) sm.ovf = 0;
-    float rm[MQ];                                                  // largest product of this lane's rows so far
+    float rm[MQ][ME];                                              // largest product so far of this lane's rows per block
 #pragma unroll
-    for (int mq = 0; mq < MQ; ++mq) rm[mq] = neg_inf();
-    auto qloc = [&](int mq) __attribute__((always_inline)) { return wq * (MQ * 32) + mq * 32 + r32; };
+    for (int mq = 0; mq < MQ; ++mq)
+#pragma unroll
+        for (int mb = 0; mb < ME; ++mb) rm[mq][mb] = neg_inf();
+    // Lane numbers for the work after a tile's MFMAs.  They go through an empty
+    // asm there, so that what follows from them is computed there and not kept
+    // in registers (or spilled) through the MFMAs.
+    int hl = h, cl = r32;
+    auto qloc = [&](int mq) __attribute__((always_inline)) { return wq * (MQ * 32) + mq * 32 + cl; };
     auto log_of = [&](int ql) __attribute__((always_inline)) { return A.log + ((q0 + ql) * splits + split) * cap; };
 
     // ---- operand reads: lane (h, r32) supplies row r32 of a block, step s of
@@ -298,7 +307,7 @@ __global__ __launch_bounds__(TL_NT) void k_tile(const TileArgs A)
                     const bool act = left > 0 && mk[mq][mb] != 0;
                     const int j = act ? __builtin_ctz(mk[mq][mb]) : 0;
                     const float sc = clamp1(tl_pick(acc[mb][mq], j) * fq) + 0.0f;      // -0 becomes +0: equal scores
-                    const int e = (int)(e0 + (we * ME + mb) * 32 + 8 * (j >> 2) + 4 * h + (j & 3));
+                    const int e = (int)(e0 + (we * ME + mb) * 32 + 8 * (j >> 2) + 4 * hl + (j & 3));
                     if (act) {
                         *p++ = q2_pack(sc, e);
                         mk[mq][mb] &= mk[mq][mb] - 1;
@@ -519,9 +528,10 @@ __global__ __launch_bounds__(TL_NT) void k_tile(const TileArgs A)
 
         // ---- filter: products times entry factors, the blocks' maxima ----
         // lane (h, c) holds, of block (mb, mq), query c and rows 8 g + 4 h + i (g, i < 4)
-        const float* fr = sm.fe[it & (TL_FR - 1)] + we * ME * 32 + 4 * h;
+        asm volatile("" : "+v"(hl), "+v"(cl));
+        const float* fr = sm.fe[it & (TL_FR - 1)] + we * ME * 32 + 4 * hl;
         float m[MQ][ME];
-        const int lim = (int)(r1 - e0 < TL_BE ? r1 - e0 : TL_BE) - we * ME * 32 - 4 * h;   // rows below it are the split's
+        const int lim = (int)(r1 - e0 < TL_BE ? r1 - e0 : TL_BE) - we * ME * 32 - 4 * hl;   // rows below it are the split's
         const bool part = r1 - e0 < TL_BE;
 #pragma unroll
         for (int mb = 0; mb < ME; ++mb) {
@@ -545,7 +555,7 @@ __global__ __launch_bounds__(TL_NT) void k_tile(const TileArgs A)
 #pragma unroll
                 for (int j = 0; j < 16; ++j) x = __builtin_fmaxf(x, acc[mb][mq][j]);
                 m[mq][mb] = x;
-                rm[mq] = __builtin_fmaxf(rm[mq], x);
+                rm[mq][mb] = __builtin_fmaxf(rm[mq][mb], x);
             }
         }
 
@@ -570,7 +580,7 @@ __global__ __launch_bounds__(TL_NT) void k_tile(const TileArgs A)
                                     float x = neg_inf();
 #pragma unroll
                                     for (int j = 0; j < 16 / GPB; ++j) x = __builtin_fmaxf(x, acc[mb][mq][g * (16 / GPB) + j]);
-                                    sm.seed[(((we * ME + mb) * 2 + h) * GPB + g) * LD + ql] = x;
+                                    sm.seed[(((we * ME + mb) * 2 + hl) * GPB + g) * LD + ql] = x;
                                 }
                         }
                     }
@@ -636,10 +646,12 @@ __global__ __launch_bounds__(TL_NT) void k_tile(const TileArgs A)
             for (int mq = 0; mq < MQ; ++mq) {
                 const int ql = qloc(mq);
                 const float fq = sm.fq[ql];
-                const float s = clamp1(rm[mq] * fq);
-                if (fq == fq && rm[mq] > neg_inf())
-                    __hip_atomic_fetch_max(A.bucket + (int64_t)((split * C::CLS + we * 2 + h) % k) * A.b_pad + q0 + ql,
-                                           q2_key(s), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                for (int mb = 0; mb < ME; ++mb)
+                    if (fq == fq && rm[mq][mb] > neg_inf())
+                        __hip_atomic_fetch_max(
+                            A.bucket + (int64_t)((split * TL_CLASSES + (we * ME + mb) * 2 + hl) % k) * A.b_pad + q0 + ql,
+                            q2_key(clamp1(rm[mq][mb] * fq)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
     }

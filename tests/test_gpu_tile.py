@@ -81,6 +81,22 @@ def test_tile_edges(apc, dtype, b, n, d, k):
     check(e, q, k, ts, ti, {"f32": 1e-5, "e4m3": 1e-4}.get(dtype, 1e-5))
 
 
+@pytest.mark.parametrize("dtype,b,n,d,k", [
+    ("f16", 16, 500000, 768, 10), ("f16", 17, 66000, 768, 10), ("bf16", 127, 65536, 768, 9), ("bf16", 128, 65536, 768, 10),
+    ("f16", 256, 65537, 768, 1), ("f16", 256, 65537, 768, 11), ("f16", 257, 65537, 768, 10),      # query-stationary or tiled
+    ("f32", 48, 2000, 256, 5), ("f32", 49, 2000, 256, 5),                                         # small float32 or tiled
+    ("e4m3", 12288, 20001, 512, 7), ("e4m3", 12288, 20000, 512, 7), ("f16", 4097, 20001, 256, 17),  # two wavefronts per SIMD or tiled
+])
+def test_routes_meet(apc, dtype, b, n, d, k):
+    """Both sides of every line between the kernels."""
+    say(f"route {dtype} b={b} n={n} d={d} k={k}")
+    e, es = rows(n, d, dtype, n + k)
+    q, qs = rows(b, d, dtype, b)
+    ts, ti = match(apc, e, es, q, qs, k)
+    r = torch.arange(0, b, max(1, b // 97), device="cuda")
+    check(e, q[r], k, ts[r], ti[r], {"f32": 1e-5, "e4m3": 1e-4}.get(dtype, 1e-5))
+
+
 @pytest.mark.parametrize("b", [60, 150])
 def test_tile_batches_of_several_passes(apc, b):
     """Rows so wide that the copy of the queries takes several passes."""
