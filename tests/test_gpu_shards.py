@@ -101,3 +101,33 @@ def test_merge_shards_offsets_near_int32_limit(apc, orc):
     assert np.array_equal(oi.cpu().numpy(), wi)
     assert np.array_equal(np.isnan(gs), np.isnan(ws)) and np.array_equal(gs[~np.isnan(ws)], ws[~np.isnan(ws)])
     assert (wi >= -1).all() and (wi[:, 0] >= 0).all()
+
+
+@pytest.mark.parametrize("g,kin,k", [(2, 8, 8), (5, 9, 16), (64, 3, 20), (3, 33, 33), (64, 64, 64), (1, 64, 5)])
+def test_merge_irregular_lists(apc, orc, g, kin, k):
+    """Lists the register merge leaves to the heads' merge: a non-candidate
+    before a candidate, negative zeros, one entry in two shards; in one query
+    each, beside regular ones."""
+    b = 9
+    say(f"merge irregular g={g} kin={kin} k={k}")
+    rng = np.random.default_rng(g * 100 + kin)
+    s, i = _shard_lists(rng, g, b, kin, 5000)
+    s[0, 1, 0], i[0, 1, 0] = np.nan, -1
+    s[g - 1, 2] = np.linspace(0.9, 0.0, kin)
+    s[g - 1, 2, kin - 1] = -0.0
+    i[g - 1, 2] = np.arange(kin)
+    off = np.arange(g, dtype=np.int32) * 5000
+    ref_s, ref_i = orc.merge_shards(s, i, off, k)
+    ts = torch.empty((b, k), dtype=torch.float32, device="cuda")
+    ti = torch.empty((b, k), dtype=torch.int32, device="cuda")
+    apc.apc_merge_shards(torch.from_numpy(s).cuda(), torch.from_numpy(i).cuda(), g, b, kin, off, k, ts, ti)
+    torch.cuda.synchronize()
+    assert np.array_equal(ti.cpu().numpy(), ref_i)
+    assert np.array_equal(ts.cpu().numpy(), ref_s, equal_nan=True)
+    if g > 1:                                            # the same shard twice: each entry once
+        s2, i2 = np.stack([s[0], s[0]]), np.stack([i[0], i[0]])
+        apc.apc_merge_shards(torch.from_numpy(s2).cuda(), torch.from_numpy(i2).cuda(), 2, b, kin, [0, 0], k, ts, ti)
+        torch.cuda.synchronize()
+        one_s, one_i = orc.merge_shards(s[:1], i[:1], off[:1], k)
+        assert np.array_equal(ti.cpu().numpy(), one_i)
+        assert np.array_equal(ts.cpu().numpy(), one_s, equal_nan=True)
