@@ -24,9 +24,10 @@ hipError_t launch_tile_f16(int bq, const TileArgs& a, hipStream_t s);
 hipError_t launch_tile_bf16(int bq, const TileArgs& a, hipStream_t s);
 hipError_t launch_tile_e4m3(int bq, const TileArgs& a, hipStream_t s);
 
-// query factors, reset buckets, and the copy of the queries: stage j (64 bytes
-// of d) of query tile t is the BQ x 64 bytes at (t nst + j) BQ 64, unit u of
-// row r at place u ^ (r / 4 % 4) of its 64 bytes; zeros past d and past b
+// query factors, reset buckets, and the copy of the queries: stage 2 c + j
+// (half j of the 128 bytes c of d) of query tile t is the BQ x 64 bytes at
+// (t nst + 2 c + j) BQ 64; unit 4 h + 2 j + s (h, j, s < 2) of row r's 128 bytes
+// is in its stage at place (2 h + s) ^ (r / 4 % 4); zeros past d and past b
 hipError_t launch_tile_prep(int dt, const void* q, const float* q_scale, int32_t b, int64_t row_bytes, int bq,
                             const TileArgs& a, float* fq, uint8_t* qcopy, hipStream_t s);
 hipError_t launch_tile(int dt, int bq, const TileArgs& a, hipStream_t s);

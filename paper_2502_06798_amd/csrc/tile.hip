@@ -44,7 +44,9 @@ __global__ __launch_bounds__(256) void k_tile_prep(const uint8_t* __restrict__ q
             v = *reinterpret_cast<const uint4*>(row + u * 16);
             sumsq16<DT>(v, ss, bad);
         }
-        *reinterpret_cast<uint4*>(to + (u >> 2) * bq * 64 + (((u & 3) ^ ((local >> 2) & 3)) * 16)) = v;
+        const int64_t stage = (u >> 3) * 2 + ((u >> 1) & 1);
+        const int place = (int)(((u >> 2) & 1) * 2 + (u & 1));
+        *reinterpret_cast<uint4*>(to + stage * bq * 64 + ((place ^ ((local >> 2) & 3)) * 16)) = v;
     }
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) ss += __shfl_xor(ss, m, 64);

@@ -261,11 +261,12 @@ __global__ __launch_bounds__(TL_NT) void k_tile(const TileArgs A)
     auto qloc = [&](int mq) __attribute__((always_inline)) { return wq * (MQ * 32) + mq * 32 + cl; };
     auto log_of = [&](int ql) __attribute__((always_inline)) { return A.log + ((q0 + ql) * splits + split) * cap; };
 
-    // ---- operand reads: lane (h, r32) supplies row r32 of a block, step s of
-    // a stage its unit 2 s + h (e4m3: units 2 h and 2 h + 1) ----
-    const int un = DT == APC_E4M3 ? 2 * h : h;
-    const uint32_t aoff = (uint32_t)((we * ME * 32 + r32) * TL_ROWB + ((un ^ ((r32 >> 1) & 7)) * 16));
-    const uint32_t boff = (uint32_t)((wq * MQ * 32 + r32) * TL_SB + ((un ^ ((r32 >> 2) & 3)) * 16));
+    // ---- operand reads: lane (h, r32) supplies row r32 of a block; step s of
+    // half j of a slot multiplies units 4 h + 2 j + s of its 128 bytes (e4m3:
+    // that and the next), which is the order of the other kernels' sums too;
+    // a stage of the queries' copy holds unit 4 h + 2 j + s at place 2 h + s ----
+    const uint32_t aoff = (uint32_t)((we * ME * 32 + r32) * TL_ROWB + (((4 * h) ^ ((r32 >> 1) & 7)) * 16));
+    const uint32_t boff = (uint32_t)((wq * MQ * 32 + r32) * TL_SB + (((2 * h) ^ ((r32 >> 2) & 3)) * 16));
     auto rd16 = [&](const uint8_t* p) __attribute__((always_inline)) {
         typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // (a load that is known to be aligned)
         return *reinterpret_cast<const u32x4*>(__builtin_assume_aligned(p, 16));
@@ -396,13 +397,13 @@ __global__ __launch_bounds__(TL_NT) void k_tile(const TileArgs A)
         constexpr int ST = TlOp<DT>::STEPS;                        // steps of a stage
         Frag a0[ME], b0[MQ], a1[ME], b1[MQ];
         auto read_b = [&](int sl, int s, Frag (&b)[MQ]) __attribute__((always_inline)) {
-            const uint32_t base = (uint32_t)sl * QSLOT + (boff ^ (uint32_t)(s * 32));
+            const uint32_t base = (uint32_t)sl * QSLOT + (boff ^ (uint32_t)(s * 16));
 #pragma unroll
             for (int mq = 0; mq < MQ; ++mq) b[mq] = rd(sm.q, base + mq * 32 * TL_SB);
         };
         // half: the even or odd stage of the slot
         auto a_at = [&](int sl, int half, int s) __attribute__((always_inline)) {
-            return (uint32_t)sl * TL_ESLOT + (aoff ^ (uint32_t)(half * TL_SB + s * 32));
+            return (uint32_t)sl * TL_ESLOT + (aoff ^ (uint32_t)(half * 32 + s * 16));
         };
         auto read_a = [&](int sl, int half, int s, Frag (&a)[ME]) __attribute__((always_inline)) {
             const uint32_t base = a_at(sl, half, s);

@@ -154,3 +154,20 @@ def test_tile_invalid_queries(apc):
     assert (ti[bad] == -1).all() and torch.isnan(ts[bad]).all()
     check(e, q[good], 9, ts[good].double(), ti[good].long(), 1e-5)
     c.close()
+
+
+@pytest.mark.parametrize("dtype,b,n,d,k", [("f16", 200, 70000, 768, 10), ("bf16", 8, 500000, 768, 5),
+                                            ("e4m3", 12288, 20001, 768, 32), ("f16", 4096, 600000, 256, 3)])
+def test_scores_do_not_depend_on_the_kernel(apc, dtype, b, n, d, k):
+    """Lists of a batch that another kernel serves, bit for bit those of the
+    tiled kernel on some of its queries: the sums run over d in one order."""
+    say(f"one order {dtype} b={b} n={n} d={d} k={k}")
+    e, es = rows(n, d, dtype, 31)
+    q, qs = rows(b, d, dtype, 32)
+    ts, ti = match(apc, e, es, q, qs, k)
+    few = min(b, 100)
+    if b < 20:                                           # more queries instead: these are served by the query-stationary kernel
+        q, few = torch.cat([q] * 5), 5 * b
+        ts, ti = torch.cat([ts] * 5), torch.cat([ti] * 5)
+    ts2, ti2 = match(apc, e, es, q[:few].contiguous(), None if qs is None else qs[:1].expand(few).contiguous(), k)
+    assert torch.equal(ts[:few], ts2) and torch.equal(ti[:few], ti2)
