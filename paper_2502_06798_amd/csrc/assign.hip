@@ -244,23 +244,196 @@ __global__ __launch_bounds__(NTB) void k_assign_reg(const AssignTable targ, cons
 __device__ inline int pref_pos(int i, int j) { return j == i ? 0 : (j < i ? i - j : j); }
 __device__ inline int pref_at(int i, int pos) { return pos == 0 ? i : (pos <= i ? i - pos : pos); }
 
-// Placement that follows a route plan x (queries of optimal level i served
-// at level j).  Same block shape and per-thread query ownership as
-// k_assign_reg.  Pass 1 ranks every query among the queries of its own level
-// in index order (per-level ballots, per-wave totals, chunks in order), which
-// also yields the batch's level histogram H.  With PLANNED the block then
-// builds the optimal plan from H, the places per level and K (one thread per
-// level, then one per plan entry) and writes it out; otherwise it reads the
-// caller's plan (negative entries count as 0).  A query of level i with rank
-// s takes the first level j of its preference list [i, i-1, .., 0, i+1, .., L]
-// where s falls below the running sum of x[i][.]; the position pos of j in
-// that list is its round.  A level admits in (round, index) order while it
-// has places, so a query's admission rank is the number of queries routed to
-// j in earlier rounds (from the realised flow) plus its rank inside group
-// (j, pos).  Only group (j, j) mixes queries of several levels; pass 2 ranks
-// its members with one ballot per such level, the others are ranked by their
-// offset in their level's quota.
-template <int QPT, int NTB, bool PLANNED>
+// Ranks of a batch's values v[c] (0..L, others: none) among equal ones in query
+// order, query q = c NTB + tid.  A segment is the 64 queries of a wavefront in a
+// chunk.  The lanes with a lane's value are found by a ballot per bit of it
+// (six for up to 33 levels, where a ballot per level took up to 33), the first
+// of them stores their count; seg[p][g] is then, after one scan per level (a
+// wavefront each), the count before segment g.  total[p]: the counts.  Four
+// barriers whatever the number of chunks.
+template <int QPT, int NTB>
+struct Ranks {
+    static constexpr int NWAVE = NTB / 64, NSEG = QPT * NWAVE;
+    static constexpr int LD = NSEG + 1;
+    int seg[APC_MAX_LEVELS + 1][LD];
+    int total[APC_MAX_LEVELS + 1];
+};
+template <int QPT, int NTB>
+__device__ inline void rank_levels(Ranks<QPT, NTB>& rk, const int (&v)[QPT], int n, int tid, int (&rank)[QPT])
+{
+    typedef Ranks<QPT, NTB> R;
+    const int lane = tid & 63, wave = tid >> 6;
+    for (int i = tid; i < n * R::LD; i += NTB) rk.seg[i / R::LD][i % R::LD] = 0;
+    const int bits = 32 - __builtin_clz(n);                        // of values 0..n - 1, and n: none
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < QPT; ++c) {
+        const int x = v[c] < 0 ? n : v[c];
+        uint64_t same = ~0ull;
+        for (int i = 0; i < bits; ++i) {
+            const uint64_t m = __ballot((x >> i) & 1);
+            same &= (x >> i) & 1 ? m : ~m;
+        }
+        rank[c] = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+        if (v[c] >= 0 && rank[c] == 0) rk.seg[v[c]][c * R::NWAVE + wave] = __popcll(same);
+    }
+    __syncthreads();
+    if constexpr (QPT == 1) {
+        // few segments: every query adds the counts of the wavefronts before its own
+        if (v[0] >= 0) {
+#pragma unroll
+            for (int w = 0; w < R::NWAVE; ++w) rank[0] += w < wave ? rk.seg[v[0]][w] : 0;
+        }
+        if (tid < n) {
+            int t = 0;
+#pragma unroll
+            for (int w = 0; w < R::NWAVE; ++w) t += rk.seg[tid][w];
+            rk.total[tid] = t;
+        }
+        __syncthreads();
+    } else {
+        for (int p = wave; p < n; p += R::NWAVE) {                 // uniform per wavefront
+            constexpr int PER = (R::NSEG + 63) / 64;
+            int x[PER], sum = 0;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int g = lane * PER + i;
+                x[i] = g < R::NSEG ? rk.seg[p][g] : 0;
+                sum += x[i];
+            }
+            int inc = sum;
+#pragma unroll
+            for (int m = 1; m < 64; m *= 2) {
+                const int o = __shfl_up(inc, m, 64);
+                if (lane >= m) inc += o;
+            }
+            int run = inc - sum;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int g = lane * PER + i;
+                if (g < R::NSEG) rk.seg[p][g] = run;
+                run += x[i];
+            }
+            if (lane == 63) rk.total[p] = inc;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < QPT; ++c)
+            if (v[c] >= 0) rank[c] += rk.seg[v[c]][c * R::NWAVE + wave];
+    }
+}
+
+// The flow x[i n + p] (queries of optimal level i placed at level p) of the
+// rounds placement, by one wavefront, lane p holding level p.  In round r level
+// i wants level i - r (r <= i) or r (r > i), in query order.  What a level has
+// left is always the last of its queries: each round takes a prefix of them.
+// So a round is a minimum of demand and places per level, except for level r
+// itself, which the levels below r and level 2 r all want: where they ask for
+// more than it has, the first in query order win, and the query at which the
+// places run out is found from the counts before each segment and the levels of
+// that segment's queries.
+template <int QPT, int NTB>
+__device__ inline void rounds_flow(const Ranks<QPT, NTB>& rk, const uint8_t* lam, const AssignTable& t, int lane, int* x)
+{
+    constexpr int NSEG = Ranks<QPT, NTB>::NSEG;
+    const int L = t.L, n = L + 1;
+    int done = 0;                                                  // of this level's queries
+    int rem = lane <= L ? rk.total[lane] : 0, room = lane <= L ? t.level_cap[lane] : 0;
+    for (int r = 0; r <= L; ++r) {
+        if (!__ballot(rem > 0)) break;                             // every query placed
+        // single sources: level lane + r into level lane
+        const int from = lane + r;
+        const bool one = lane <= L && from <= L && (lane != r || r == 0);
+        const int want = __shfl(rem, from & 63, 64);
+        const int take = one ? (want < room ? want : room) : 0;
+        if (one) x[from * n + lane] = take;
+        // level r >= 1: sources below r and 2 r
+        const bool src = r > 0 && lane <= L && (lane < r || lane == 2 * r);
+        int ask = src ? rem : 0;
+        int total = ask;
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) total += __shfl_xor(total, m, 64);
+        const int places = __builtin_amdgcn_readlane(room, r);
+        if (r > 0 && total > places) {                             // uniform
+            // segments whose preceding applicants fit (a prefix): the last one is where places run out
+            constexpr int PER = (NSEG + 63) / 64;
+            int c[PER];
+#pragma unroll
+            for (int j = 0; j < PER; ++j) c[j] = 0;
+            for (int i = 0; i <= L; ++i)
+                if (i < r || i == 2 * r) {
+                    const int d = __builtin_amdgcn_readlane(done, i);
+#pragma unroll
+                    for (int j = 0; j < PER; ++j) {
+                        const int over = rk.seg[i][j * 64 + lane < NSEG ? j * 64 + lane : 0] - d;
+                        c[j] += over > 0 ? over : 0;
+                    }
+                }
+            int g = 0;
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                const uint64_t fit = __ballot(j * 64 + lane < NSEG && c[j] <= places);
+                if (fit) g = j * 64 + 63 - __builtin_clzll(fit);
+            }
+            const int mine = lam[g * 64 + lane];                   // 255 past the batch
+            const int start = lane <= L ? rk.seg[lane][g] : 0;     // this level's count before the segment
+            const int ahead = src && start > done ? start - done : 0;   // its applicants before the segment
+            int before = ahead;
+#pragma unroll
+            for (int m = 32; m >= 1; m >>= 1) before += __shfl_xor(before, m, 64);
+            uint64_t apps = 0;                                     // the segment's applicants
+            for (int i = 0; i <= L; ++i)
+                if (i < r || i == 2 * r) {
+                    const int d = __builtin_amdgcn_readlane(done, i), s0 = __builtin_amdgcn_readlane(start, i);
+                    const uint64_t m = __ballot(mine == i);
+                    const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                    apps |= __ballot(mine == i && s0 + rank >= d);
+                }
+            const int nth = __builtin_amdgcn_mbcnt_hi((uint32_t)(apps >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)apps, 0u));
+            const uint64_t won = apps & __ballot(nth < places - before);
+            ask = ahead;
+            for (int i = 0; i <= L; ++i)
+                if (i < r || i == 2 * r) {
+                    const int c1 = __popcll(won & __ballot(mine == i));
+                    if (lane == i) ask += c1;
+                }
+        }
+        if (src) x[lane * n + r] = ask;
+        // what is left
+        const int gone = __shfl(take, (lane - r) & 63, 64);        // by level lane - r
+        if (src) {
+            rem -= ask;
+            done += ask;
+        } else if (lane <= L && lane >= r) {
+            rem -= gone;
+            done += gone;
+        }
+        const int got = total < places ? total : places;
+        if (lane == r && r > 0) room -= got;
+        else room -= take;
+    }
+}
+
+// Placement by rounds (MODE 2) or by a route plan x (queries of optimal level i
+// served at level j): read from the caller (MODE 0; negative entries count as
+// 0) or the optimal one, built from the batch's level histogram H, the places
+// per level and K (one thread per level, then one per plan entry) and written
+// out (MODE 1).  The rounds are a plan too, whose flow one wavefront finds
+// (rounds_flow).  Same query ownership as k_assign_reg.  Pass 1 ranks every
+// query among the queries of its own level in index order, which also yields
+// H.  A query of level i with rank s takes the first level j of its preference
+// list [i, i-1, .., 0, i+1, .., L] where s falls below the running sum of
+// x[i][.]; the position pos of j in that list is its round.  A level admits in
+// (round, index) order while it has places, so a query's admission rank is the
+// number of queries routed to j in earlier rounds (from the realised flow) plus
+// its rank inside group (j, pos).  Only group (j, j) mixes queries of several
+// levels; pass 2 ranks its members, the others are ranked by their offset in
+// their level's quota.
+// 16,384 queries, 10 levels: rounds 281 us in k_assign_reg (two barriers and a
+// ballot per level for each of 16 chunks in every round), ROUNDS_NOW here; by
+// plan 97 us with a barrier pair per chunk, PLAN_NOW now.
+enum { PLAN_GIVEN = 0, PLAN_OPTIMAL = 1, PLAN_ROUNDS = 2 };
+template <int QPT, int NTB, int MODE>
 __global__ __launch_bounds__(NTB) void k_assign_plan(const AssignTable targ, const float* __restrict__ top_score,
                                                      int32_t ld, int32_t b, int32_t* __restrict__ plan,
                                                      int32_t* __restrict__ opt_level,
@@ -269,18 +442,18 @@ __global__ __launch_bounds__(NTB) void k_assign_plan(const AssignTable targ, con
                                                      int32_t* __restrict__ out_slot,
                                                      int32_t* __restrict__ inst_fill)
 {
-    constexpr int NT = NTB, NWAVE = NTB / 64, NL = APC_MAX_LEVELS + 1;
-    __shared__ int cnt[2][NL];
-    __shared__ int wcnt[NWAVE][NL];
+    constexpr int NT = NTB, NL = APC_MAX_LEVELS + 1;
+    __shared__ Ranks<QPT, NTB> rkl;
+    __shared__ uint8_t lams[MODE == PLAN_ROUNDS ? QPT * NTB : 1];
     __shared__ int xs[NL * NL];
     __shared__ int fs[NL * NL];                              // realised flow, level i -> level j
     __shared__ int gb[NL * NL];                              // [j * n + pos]: places before group (j, pos)
+    __shared__ int cum[NL * NL];                             // [i * n + pos]: queries of level i placed up to position pos
     __shared__ int used[NL];                                 // places taken per level
-    __shared__ int cnt2[2][NL];
     __shared__ PlanWork w;
     __shared__ unsigned long long multi;                     // bit j: group (j, j) has members
     __shared__ AssignTable t;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x;
     float best[QPT];
 #pragma unroll
     for (int c = 0; c < QPT; ++c) {
@@ -289,52 +462,32 @@ __global__ __launch_bounds__(NTB) void k_assign_plan(const AssignTable targ, con
     }
     table_to_lds<NT>(targ, t, tid);
     const int L = t.L, n = L + 1;
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const int nchunk = (b + NT - 1) / NT;
     int lam[QPT], rs[QPT], dr[QPT], ik[QPT], rk[QPT];
 #pragma unroll
     for (int c = 0; c < QPT; ++c) {
         const int q = c * NT + tid;
-        lam[c] = -1;
+        lam[c] = q < b ? 0 : -1;
         rk[c] = -1;
-        if (q < b) {
-            lam[c] = 0;
-            for (int l = 0; l < L; ++l) lam[c] += best[c] >= t.theta[l];
-        }
     }
-    if (tid <= L) cnt[0][tid] = 0;
-    int cur = 0;
+    for (int l = 0; l < L; ++l) {
+        const float th = t.theta[l];
+#pragma unroll
+        for (int c = 0; c < QPT; ++c)
+            lam[c] += lam[c] >= 0 && best[c] >= th;
+    }
+    if (MODE == PLAN_ROUNDS) {
+#pragma unroll
+        for (int c = 0; c < QPT; ++c) lams[c * NT + tid] = (uint8_t)lam[c];   // 255 past the batch
+    }
     // Pass 1: rank among the queries of the same level; the histogram.
-#pragma unroll
-    for (int c = 0; c < QPT; ++c) {
-        if (c < nchunk) {                                     // uniform
-            int pre = 0;
-            for (int p = 0; p <= L; ++p) {
-                const uint64_t m = __ballot(lam[c] == p);
-                if (lam[c] == p) pre = __popcll(m & lt_mask);
-                if (lane == 0) wcnt[wave][p] = __popcll(m);
-            }
-            __syncthreads();
-            if (lam[c] >= 0) {
-                int r = cnt[cur][lam[c]] + pre;
-#pragma unroll
-                for (int ww = 0; ww < NWAVE; ++ww) r += ww < wave ? wcnt[ww][lam[c]] : 0;
-                rs[c] = r;
-            }
-            if (tid <= L) {
-                int tot = cnt[cur][tid];
-#pragma unroll
-                for (int ww = 0; ww < NWAVE; ++ww) tot += wcnt[ww][tid];
-                cnt[cur ^ 1][tid] = tot;
-            }
-            __syncthreads();
-            cur ^= 1;
-        }
-    }
-    __syncthreads();                                          // b = 0: cnt[0] initialised
+    rank_levels<QPT, NTB>(rkl, lam, n, tid, rs);
     // The plan.
-    if (PLANNED) {
-        if (tid <= L) plan_level_own(L, cnt[cur], t.level_cap, tid, w);
+    if (MODE == PLAN_ROUNDS) {
+        for (int e = tid; e < n * n; e += NT) xs[e] = 0;
+        __syncthreads();
+        if (tid < 64) rounds_flow<QPT, NTB>(rkl, lams, t, tid, xs);
+    } else if (MODE == PLAN_OPTIMAL) {
+        if (tid <= L) plan_level_own(L, rkl.total, t.level_cap, tid, w);
         __syncthreads();
         if (tid < L) plan_level_flow(L, tid, w);
         if (tid == L) w.n[L] = 0;
@@ -355,7 +508,7 @@ __global__ __launch_bounds__(NTB) void k_assign_plan(const AssignTable targ, con
     __syncthreads();
     // Realised flow: how many of level i's queries the plan sends to level j
     // (the row's quotas taken in preference order until the level runs out).
-    const int* H = cnt[cur];
+    const int* H = rkl.total;
     for (int e = tid; e < n * n; e += NT) {
         const int i = e / n, j = e - i * n, pj = pref_pos(i, j);
         int64_t before = 0;
@@ -363,6 +516,9 @@ __global__ __launch_bounds__(NTB) void k_assign_plan(const AssignTable targ, con
         int64_t f = (int64_t)H[i] - before;
         f = f < 0 ? 0 : (f > xs[e] ? xs[e] : f);
         fs[e] = (int)f;
+        // queries of level i that go to positions up to pj (its quotas' running sum, at most H)
+        const int64_t upto = before + xs[e];
+        cum[i * n + pj] = upto < H[i] ? (int)upto : H[i];
     }
     if (tid == 0) multi = 0ull;
     __syncthreads();
@@ -375,9 +531,13 @@ __global__ __launch_bounds__(NTB) void k_assign_plan(const AssignTable targ, con
     }
     if (tid <= L) {
         int tot = 0;
-        for (int i = 0; i <= L; ++i) tot += fs[i * n + tid];
+        int mixed = 0;                                       // members of group (tid, tid)
+        for (int i = 0; i <= L; ++i) {
+            tot += fs[i * n + tid];
+            mixed += tid > 0 && pref_pos(i, tid) == tid ? fs[i * n + tid] : 0;
+        }
+        if (mixed) atomicOr(&multi, 1ull << tid);
         used[tid] = tot < t.level_cap[tid] ? tot : t.level_cap[tid];
-        cnt2[0][tid] = 0;
     }
     // Destination, position and rank inside its group (j, pos).  A group with
     // pos != j holds queries of one level i only (i = j + pos, or i = j for
@@ -388,54 +548,33 @@ __global__ __launch_bounds__(NTB) void k_assign_plan(const AssignTable targ, con
     for (int c = 0; c < QPT; ++c) {
         dr[c] = -1;
         ik[c] = -1;
-        if (c < nchunk && lam[c] >= 0) {
+        if (lam[c] >= 0) {
+            // the first position whose running sum passes the rank (the sums rise with it)
             const int i = lam[c];
-            int64_t acc = 0;
-            for (int pos = 0; pos <= L; ++pos) {
-                const int j = pref_at(i, pos);
-                const int x = xs[i * n + j];
-                acc += x;
-                if (rs[c] < acc) {
-                    dr[c] = j | (pos << 8);
-                    if (pos == j && j > 0) atomicOr(&multi, 1ull << j);
-                    else ik[c] = rs[c] - (int)(acc - x);
-                    break;
+            const int* row = cum + i * n;
+            int lo = 0, hi = L;
+            if (rs[c] < row[L]) {
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (rs[c] < row[mid]) hi = mid;
+                    else lo = mid + 1;
                 }
+                const int pos = lo, j = pref_at(i, pos);
+                dr[c] = j | (pos << 8);
+                if (pos != j || j == 0) ik[c] = rs[c] - (pos > 0 ? row[pos - 1] : 0);
             }
         }
     }
     __syncthreads();
     const unsigned long long mm = multi;
-    cur = 0;
     if (mm) {                                                 // uniform
+        int g[QPT], r2[QPT];
 #pragma unroll
-        for (int c = 0; c < QPT; ++c) {
-            if (c < nchunk) {                                 // uniform
-                const int g = (dr[c] >= 0 && ik[c] < 0) ? (dr[c] & 0xff) : -1;
-                int pre = 0;
-                for (unsigned long long bits = mm; bits; bits &= bits - 1) {
-                    const int j = __builtin_ctzll(bits);
-                    const uint64_t m = __ballot(g == j);
-                    if (g == j) pre = __popcll(m & lt_mask);
-                    if (lane == 0) wcnt[wave][j] = __popcll(m);
-                }
-                __syncthreads();
-                if (g >= 0) {
-                    int r = cnt2[cur][g] + pre;
+        for (int c = 0; c < QPT; ++c) g[c] = dr[c] >= 0 && ik[c] < 0 ? (dr[c] & 0xff) : -1;
+        rank_levels<QPT, NTB>(rkl, g, n, tid, r2);
 #pragma unroll
-                    for (int ww = 0; ww < NWAVE; ++ww) r += ww < wave ? wcnt[ww][g] : 0;
-                    ik[c] = r;
-                }
-                if (tid <= L && ((mm >> tid) & 1ull)) {
-                    int tot = cnt2[cur][tid];
-#pragma unroll
-                    for (int ww = 0; ww < NWAVE; ++ww) tot += wcnt[ww][tid];
-                    cnt2[cur ^ 1][tid] = tot;
-                }
-                __syncthreads();
-                cur ^= 1;
-            }
-        }
+        for (int c = 0; c < QPT; ++c)
+            if (g[c] >= 0) ik[c] = r2[c];
     }
     // Admission rank at the level: earlier groups, then the rank in the group.
 #pragma unroll
@@ -474,19 +613,19 @@ __global__ __launch_bounds__(NTB) void k_assign_plan(const AssignTable targ, con
         }
 }
 
-template <bool PLANNED>
+template <int MODE>
 hipError_t launch_plan_t(const AssignTable& t, const float* top_score, int32_t ld, int32_t b, int32_t* plan,
                          int32_t* opt_level, int32_t* out_level, int32_t* out_inst, int32_t* out_slot,
                          int32_t* inst_fill, hipStream_t s)
 {
     if (b <= 256)
-        k_assign_plan<1, 256, PLANNED><<<1, 256, 0, s>>>(t, top_score, ld, b, plan, opt_level, out_level, out_inst, out_slot, inst_fill);
+        k_assign_plan<1, 256, MODE><<<1, 256, 0, s>>>(t, top_score, ld, b, plan, opt_level, out_level, out_inst, out_slot, inst_fill);
     else if (b <= NT)
-        k_assign_plan<1, NT, PLANNED><<<1, NT, 0, s>>>(t, top_score, ld, b, plan, opt_level, out_level, out_inst, out_slot, inst_fill);
+        k_assign_plan<1, NT, MODE><<<1, NT, 0, s>>>(t, top_score, ld, b, plan, opt_level, out_level, out_inst, out_slot, inst_fill);
     else if (b <= 4 * NT)
-        k_assign_plan<4, NT, PLANNED><<<1, NT, 0, s>>>(t, top_score, ld, b, plan, opt_level, out_level, out_inst, out_slot, inst_fill);
+        k_assign_plan<4, NT, MODE><<<1, NT, 0, s>>>(t, top_score, ld, b, plan, opt_level, out_level, out_inst, out_slot, inst_fill);
     else if (b <= 16 * NT)
-        k_assign_plan<16, NT, PLANNED><<<1, NT, 0, s>>>(t, top_score, ld, b, plan, opt_level, out_level, out_inst, out_slot, inst_fill);
+        k_assign_plan<16, NT, MODE><<<1, NT, 0, s>>>(t, top_score, ld, b, plan, opt_level, out_level, out_inst, out_slot, inst_fill);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
@@ -502,10 +641,9 @@ hipError_t launch_assign(const AssignTable& t, const float* top_score, int32_t l
         k_assign_reg<1, 256><<<1, 256, 0, s>>>(t, top_score, ld, b, opt_level, out_level, out_inst, out_slot, inst_fill);
     else if (b <= NT)
         k_assign_reg<1, NT><<<1, NT, 0, s>>>(t, top_score, ld, b, opt_level, out_level, out_inst, out_slot, inst_fill);
-    else if (b <= 4 * NT)
-        k_assign_reg<4, NT><<<1, NT, 0, s>>>(t, top_score, ld, b, opt_level, out_level, out_inst, out_slot, inst_fill);
-    else if (b <= 16 * NT)
-        k_assign_reg<16, NT><<<1, NT, 0, s>>>(t, top_score, ld, b, opt_level, out_level, out_inst, out_slot, inst_fill);
+    else if (b <= 16 * NT)                               // several queries per thread: the rounds as a plan
+        return launch_plan_t<PLAN_ROUNDS>(t, top_score, ld, b, nullptr, opt_level, out_level, out_inst, out_slot,
+                                          inst_fill, s);
     else
         k_assign<<<1, NT, 0, s>>>(t, top_score, ld, b, opt_level, out_level, out_inst, out_slot, inst_fill);
     return hipGetLastError();
@@ -516,8 +654,8 @@ hipError_t launch_assign_plan(const AssignTable& t, bool planned, const float* t
                               int32_t* out_slot, int32_t* inst_fill, hipStream_t s)
 {
     static_assert(16 * NT == APC_MAX_ROUTED_BATCH, "largest routed batch");
-    return planned ? launch_plan_t<true>(t, top_score, ld, b, plan, opt_level, out_level, out_inst, out_slot, inst_fill, s)
-                   : launch_plan_t<false>(t, top_score, ld, b, plan, opt_level, out_level, out_inst, out_slot, inst_fill, s);
+    return planned ? launch_plan_t<PLAN_OPTIMAL>(t, top_score, ld, b, plan, opt_level, out_level, out_inst, out_slot, inst_fill, s)
+                   : launch_plan_t<PLAN_GIVEN>(t, top_score, ld, b, plan, opt_level, out_level, out_inst, out_slot, inst_fill, s);
 }
 
 }  // namespace apc

@@ -124,7 +124,9 @@ void run_row_factors(int64_t n, int64_t row_bytes, const uint8_t* r, const float
                      int64_t n_slots, float* f, BuildStatus* st, uint8_t* rowflags, hipStream_t s)
 {
     auto grid = [n](int64_t per) { return dim3((unsigned)((n + per - 1) / per)); };
-    if (row_bytes <= 8 * 16 * 16)
+    if (n <= 2048)                                         // a batch of queries: every row's loads at once
+        k_row_factors<DT, 64, 1><<<grid(4), 256, 0, s>>>(r, n, row_bytes, scale, slots, n_slots, f, st, rowflags);
+    else if (row_bytes <= 8 * 16 * 16)
         k_row_factors<DT, 16, 2><<<grid(32), 256, 0, s>>>(r, n, row_bytes, scale, slots, n_slots, f, st, rowflags);
     else if (row_bytes <= 8 * 32 * 16)
         k_row_factors<DT, 32, 2><<<grid(16), 256, 0, s>>>(r, n, row_bytes, scale, slots, n_slots, f, st, rowflags);

@@ -388,3 +388,33 @@ def test_gather_bit_exact(apc, orc):
     assert np.array_equal(hit.cpu().numpy(), h) and h.sum() > 0
     assert np.array_equal(batch.cpu().numpy(), want)
     c.close()
+
+
+@pytest.mark.parametrize("b,L,I,tight", [(1025, 5, 7, 0.3), (4096, 10, 12, 1.0), (4097, 10, 40, 0.5), (8000, 32, 256, 0.9),
+                                          (16384, 10, 32, 1.0), (16384, 1, 2, 0.6), (16383, 32, 33, 0.2), (3000, 0, 3, 0.5)])
+def test_assign_rounds_of_large_batches(apc, orc, b, L, I, tight):
+    """Batches of several queries per thread: levels that run out of places
+    while several levels ask for them, at random points of the batch."""
+    say(f"assign rounds b={b} L={L} I={I} tight={tight}")
+    rng = np.random.default_rng(b + L * 7 + I)
+    theta = np.sort(rng.uniform(-0.5, 0.9, L)).astype(np.float32)
+    K = np.arange(1, L + 1, dtype=np.int32) * 5
+    best = rng.uniform(-1, 1, b).astype(np.float32)
+    best[: b // 3] = np.sort(best[: b // 3])                 # long runs of one level, then a mixture
+    lvl = rng.integers(0, L + 1, I).astype(np.int32)
+    share = rng.dirichlet(np.full(I, 0.5)) * b * tight
+    cap = np.floor(share).astype(np.int32)
+    queue = rng.integers(0, 9, I).astype(np.int32)
+    ts = torch.from_numpy(best).cuda().reshape(b, 1).contiguous()
+    i32 = dict(dtype=torch.int32, device="cuda")
+    o = [torch.full((b,), -9, **i32) for _ in range(4)]
+    fill = torch.full((I,), -9, **i32)
+    apc.apc_assign(ts, 1, b, theta, K, lvl, cap, queue, *o, fill)
+    torch.cuda.synchronize()
+    opt = orc.levels(best.astype(np.float64), theta)
+    r = orc.assign(opt, L, lvl, cap, queue)
+    got = [x.cpu().numpy() for x in o]
+    assert np.array_equal(got[0], opt)
+    for a, w in zip(got[1:], r[:3]):
+        assert np.array_equal(a, w)
+    assert np.array_equal(fill.cpu().numpy(), np.asarray(r[3]) if len(r) > 3 else np.bincount(r[1][r[1] >= 0], minlength=I))
