@@ -341,30 +341,45 @@ __global__ __launch_bounds__(TL_NT) void k_tile(const TileArgs A)
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wavefront's log stores
             __syncthreads();
             if (tid == 0) sm.ovf = 0;
+            // four logs at a time: their loads go out together
+            constexpr int CQ = BQ / TL_NW < 4 ? BQ / TL_NW : 4;
 #pragma unroll 1
-            for (int ql = wave; ql < BQ; ql += TL_NW) {
-                int c = *(volatile int*)&sm.cnt[ql];
-                if (c <= cap - cap / 4) continue;                  // uniform; at least k of them
-                c = c < cap ? c : cap;
-                uint64_t* lg = log_of(ql);
-                uint64_t x0 = 0, x1 = 0;
-                if (lane < c) x0 = __hip_atomic_load(lg + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (lane + 64 < c) x1 = __hip_atomic_load(lg + lane + 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                uint64_t kth = 0;                                  // the k-th largest key, bit by bit
-#pragma unroll 1
-                for (int bit = 63; bit >= 0; --bit) {
-                    const uint64_t t = kth | (1ull << bit);
-                    const int m = __builtin_popcountll(__builtin_amdgcn_ballot_w64(x0 >= t)) +
-                                  __builtin_popcountll(__builtin_amdgcn_ballot_w64(x1 >= t));
-                    if (m >= k) kth = t;
+            for (int q4 = wave * CQ; q4 < BQ; q4 += TL_NW * CQ) {
+                uint64_t x0[CQ], x1[CQ];
+                int c[CQ];
+#pragma unroll
+                for (int i = 0; i < CQ; ++i) {
+                    const int v = __builtin_amdgcn_readfirstlane(*(volatile int*)&sm.cnt[q4 + i]);
+                    c[i] = v <= cap - cap / 4 ? 0 : v < cap ? v : cap;   // at least k of them, or the log stays
+                    const uint64_t* lg = log_of(q4 + i);
+                    x0[i] = lane < c[i] ? __hip_atomic_load(lg + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+                    x1[i] = lane + 64 < c[i] ? __hip_atomic_load(lg + lane + 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
                 }
-                const uint64_t m0 = __builtin_amdgcn_ballot_w64(x0 >= kth), m1 = __builtin_amdgcn_ballot_w64(x1 >= kth);
-                const uint64_t below = (1ull << lane) - 1ull;
-                if (x0 >= kth) lg[__builtin_popcountll(m0 & below)] = x0;
-                if (x1 >= kth) lg[__builtin_popcountll(m0) + __builtin_popcountll(m1 & below)] = x1;
-                if (lane == 0) {
-                    sm.cnt[ql] = k;
-                    sm.f[ql] = __builtin_fmaxf(sm.f[ql], q2_key_score(kth));
+#pragma unroll
+                for (int i = 0; i < CQ; ++i) {
+                    if (c[i] == 0) continue;                       // uniform
+                    // every pair's rank, by counting the larger keys (keys are unique)
+                    int r0 = 0, r1 = 0;
+                    auto count = [&](uint64_t x, int m) __attribute__((always_inline)) {
+                        for (int j = 0; j < m; ++j) {
+                            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, j);
+                            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), j);
+                            const uint64_t t = ((uint64_t)hi << 32) | lo;
+                            r0 += t > x0[i];
+                            r1 += t > x1[i];
+                        }
+                    };
+                    count(x0[i], c[i] < 64 ? c[i] : 64);
+                    count(x1[i], c[i] - 64);
+                    uint64_t* lg = log_of(q4 + i);
+                    const bool in0 = lane < c[i] && r0 < k, in1 = lane + 64 < c[i] && r1 < k;
+                    if (in0) lg[r0] = x0[i];
+                    if (in1) lg[r1] = x1[i];
+                    if ((in0 && r0 == k - 1) || (in1 && r1 == k - 1)) {
+                        const float F = q2_key_score(in0 && r0 == k - 1 ? x0[i] : x1[i]);
+                        sm.cnt[q4 + i] = k;
+                        sm.f[q4 + i] = __builtin_fmaxf(sm.f[q4 + i], F);
+                    }
                 }
             }
             __syncthreads();
@@ -642,14 +657,19 @@ __global__ __launch_bounds__(TL_NT) void k_tile(const TileArgs A)
         if (any) append();
 
         // ---- the bound shared by all splits ----
+        // (a maximum that is not above this workgroup's bound cannot raise the
+        // smallest bucket above it; without this, 256 splits x 16 maxima of a query
+        // met in one bucket for k = 1: 64 x 28,549 x 1,024 f16 took 109 us,
+        // 39 now)
         if (A.buckets && (it & (it + 1)) == 0) {                   // after tiles 1, 2, 4, 8, ..
 #pragma unroll
             for (int mq = 0; mq < MQ; ++mq) {
                 const int ql = qloc(mq);
-                const float fq = sm.fq[ql];
+                const float F = *(volatile float*)&sm.f[ql], fq = sm.fq[ql];
 #pragma unroll
                 for (int mb = 0; mb < ME; ++mb)
-                    if (fq == fq && rm[mq][mb] > neg_inf())
+                    // (a query with a NaN factor logs nothing, whatever its bound)
+                    if (rm[mq][mb] > neg_inf() && clamp1(rm[mq][mb] * fq) > F)
                         __hip_atomic_fetch_max(
                             A.bucket + (int64_t)((split * TL_CLASSES + (we * ME + mb) * 2 + hl) % k) * A.b_pad + q0 + ql,
                             q2_key(clamp1(rm[mq][mb] * fq)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
