@@ -90,12 +90,12 @@ hipError_t launch_qs8(const MatchPlan& p, int dt, int64_t n, int32_t d, const vo
 
 // float32 caches of at most 512 blocks of 32 rows, d a multiple of 64, k <= 32,
 // b <= 48: one workgroup per 32-row block and 16-query tile, four wavefronts
-// over d (f32small.hip); the query factors come first from launch_row_factors
+// over d (f32small.hip); writes the query factors to fq
 bool f32s_fits(int dt, int64_t n, int32_t d, int32_t b, int32_t k);
 int f32s_queries();
 int f32s_rows();
 hipError_t launch_f32s(const MatchPlan& p, int64_t n, int32_t d, const void* emb, const float* fe, const void* q,
-                       const float* fq, int32_t b, int32_t k, float* ps, int* pi, hipStream_t s);
+                       float* fq, int32_t b, int32_t k, float* ps, int* pi, hipStream_t s);
 
 // ---- assignment ------------------------------------------------------------
 struct AssignTable {

@@ -9,8 +9,10 @@
 // 16); the partial sums meet in LDS.  A lane of wavefront w supplies, at
 // step (t, j), row i = lane % 16 and column w d/NW + 16 t + 4 (lane / 16) + j
 // of both operands, so the two operands see the same column for every
-// product and each lane reads 16 contiguous bytes of its row per step.  Every query's 32 scores then give the block's
-// partial list (k best, sorted by score desc then entry asc, each pair placed
+// product and each lane reads 16 contiguous bytes of its row per step.  The
+// query operands also give the queries' factors, which took a launch of their
+// own (the step of 16 x 10,000 x 768: 35.2 us with it, 33.9 without).
+// Every query's 32 scores then give the block's partial list (k best, sorted by score desc then entry asc, each pair placed
 // by its rank; rows past the cache are -inf), which k_topk_merge merges over
 // the blocks.
 #include <type_traits>
@@ -34,11 +36,12 @@ __device__ inline float fs_clamp1(float x) { return __builtin_fminf(__builtin_fm
 template <int FS_NW>
 __global__ __launch_bounds__(FS_NW * 64) void k_f32s(const float* __restrict__ emb, const float* __restrict__ fe,
                                                     int64_t n, int32_t d, const float* __restrict__ q,
-                                                    const float* __restrict__ fq, int32_t b, int32_t k, int splits,
+                                                    float* __restrict__ fq, int32_t b, int32_t k, int splits,
                                                     float* __restrict__ part_s, int* __restrict__ part_i)
 {
     __shared__ f32x4 red[FS_NW][2][64];
     __shared__ float sc[FS_QT][FS_ROWS + 1];
+    __shared__ float qss[FS_NW][64];                      // the queries' sums of squares, per wavefront and lane
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i16 = lane & 15, kq = lane >> 4;
     const int split = blockIdx.x;
@@ -54,6 +57,7 @@ __global__ __launch_bounds__(FS_NW * 64) void k_f32s(const float* __restrict__ e
     const float* pb = emb + rb * d + c0;
     const float* pq = q + qq * d + c0;
     f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+    float ss = 0.f;                                       // of this lane's elements of its query
     // steps of 16 columns, in chunks of CH, two chunk buffers: the next
     // chunk's loads are in flight while a chunk's MFMAs run
     constexpr int CH = 4;
@@ -75,6 +79,7 @@ __global__ __launch_bounds__(FS_NW * 64) void k_f32s(const float* __restrict__ e
         for (int j = 0; j < CH; ++j)
             if (t0 + j < nt) {
                 const float4 x0 = a[bf][j], x1 = c[bf][j], yq = y[bf][j];
+                ss = fmaf(yq.x, yq.x, fmaf(yq.y, yq.y, fmaf(yq.z, yq.z, fmaf(yq.w, yq.w, ss))));
                 acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(x0.x, yq.x, acc0, 0, 0, 0);
                 acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(x1.x, yq.x, acc1, 0, 0, 0);
                 acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(x0.y, yq.y, acc0, 0, 0, 0);
@@ -96,6 +101,7 @@ __global__ __launch_bounds__(FS_NW * 64) void k_f32s(const float* __restrict__ e
     }
     red[wave][0][lane] = acc0;
     red[wave][1][lane] = acc1;
+    qss[wave][lane] = ss;
     __syncthreads();
 
     // wavefront 0: the parts of d summed in a fixed order, times the
@@ -103,7 +109,15 @@ __global__ __launch_bounds__(FS_NW * 64) void k_f32s(const float* __restrict__ e
     // against query l % 16.
     if (wave == 0) {
         const int64_t qg = q0 + i16;
-        const float f = qg < b ? fq[qg] : 0.f;
+        // the query's factor: its parts of d summed in a fixed order (an element
+        // that is not finite makes the sum inf or NaN)
+        float t = 0.f;
+#pragma unroll
+        for (int w = 0; w < FS_NW; ++w) t += qss[w][lane];
+        t += __shfl_xor(t, 16, 64);
+        t += __shfl_xor(t, 32, 64);
+        const float f = __builtin_isfinite(t) && t > 0.f ? 1.0f / __builtin_sqrtf(t) : __int_as_float(0x7fc00000);
+        if (split == 0 && kq == 0 && qg < b) fq[qg] = f;   // for the merge, which marks queries that cannot be matched
 #pragma unroll
         for (int tl = 0; tl < 2; ++tl) {
             f32x4 s = red[0][tl][lane];
@@ -151,7 +165,7 @@ int f32s_queries() { return FS_QT; }
 int f32s_rows() { return FS_ROWS; }
 
 hipError_t launch_f32s(const MatchPlan& p, int64_t n, int32_t d, const void* emb, const float* fe, const void* q,
-                       const float* fq, int32_t b, int32_t k, float* ps, int* pi, hipStream_t s)
+                       float* fq, int32_t b, int32_t k, float* ps, int* pi, hipStream_t s)
 {
     const dim3 grid((unsigned)p.splits, (unsigned)p.qtiles);
     const float* e = static_cast<const float*>(emb);

@@ -353,7 +353,6 @@ hipError_t launch_match(const MatchPlan& p, int dt, int64_t n, int32_t d, const 
         }
         return hipSuccess;
     } else if (p.kernel == KERNEL_F32S) {
-        if ((e = launch_row_factors(dt, b, d, q, q_scale, nullptr, 0, fq, nullptr, s)) != hipSuccess) return e;
         if (ev_start && (e = hipEventRecord(ev_start, s)) != hipSuccess) return e;
         e = launch_f32s(p, n, d, emb, fe, q, fq, b, k, ps, pi, s);
     } else if (p.kernel == KERNEL_QS) {
