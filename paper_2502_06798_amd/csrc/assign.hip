@@ -430,8 +430,8 @@ __device__ inline void rounds_flow(const Ranks<QPT, NTB>& rk, const uint8_t* lam
 // levels; pass 2 ranks its members, the others are ranked by their offset in
 // their level's quota.
 // 16,384 queries, 10 levels: rounds 281 us in k_assign_reg (two barriers and a
-// ballot per level for each of 16 chunks in every round), ROUNDS_NOW here; by
-// plan 97 us with a barrier pair per chunk, PLAN_NOW now.
+// ballot per level for each of 16 chunks in every round), 63 here; the call by
+// plan 61 us with a barrier pair per chunk, 42 now.
 enum { PLAN_GIVEN = 0, PLAN_OPTIMAL = 1, PLAN_ROUNDS = 2 };
 template <int QPT, int NTB, int MODE>
 __global__ __launch_bounds__(NTB) void k_assign_plan(const AssignTable targ, const float* __restrict__ top_score,
