@@ -250,15 +250,20 @@ MatchPlan plan_kernel(int dt, int64_t n, int32_t d, int32_t b, int32_t k)
         if (splits > ngr) splits = ngr;
         if (splits < 1) splits = 1;
         p.splits = (int)splits;
-    } else if (q2b > 0 && ((b >= 128 && b <= 256 && n >= 65536 && n < 1000000) || (b <= 16 && n >= 500000))) {
+    } else if (q2b > 0 && ((b >= 128 && b <= 256 && n >= 65536 && n < 1000000) || (b <= 16 && n >= 500000) ||
+                               (b >= 512 && n <= 131072 && (n >= 8192 || b >= 2560)))) {
         // 16-bit rows of 1536 bytes, k <= 10: queries in VGPRs, cache rows through
         // LDS, one workgroup per CU; the query tiles of a split share an XCD.
         // For one or two tiles of 128 queries, and for the fewest queries against
         // a large cache, it is still ahead of the tiled kernel (256 x 100,000: 76
         // us and 85; 200 x 200,000: 114 and 128; 128 x 100,000: 63 and 67; 1 x
-        // 1,000,000: 270 and 276; 4 x 1,000,000: 275 and 278), elsewhere it is not
-        // (32 x 1,000,000: 289 and 286; 100 x 100,000: 60 and 57; 256 x 1,000,000:
-        // 504 and 497; 1,024 x 1,000,000: 1,660 and 1,490)
+        // 1,000,000: 270 and 276; 4 x 1,000,000: 275 and 278), and for large
+        // batches against a small one (600 x 30,000: 57 and 68; 1,024 x 60,000: 128
+        // and 142; 2,639 x 5,728: 43 and 51; 8,192 x 1,000: 70 and 95; 16,384 x
+        // 12,000: 397 and 599; 16,384 x 100,000: 2,626 and 2,806); elsewhere it is
+        // not (32 x 1,000,000: 289 and 286; 100 x 100,000: 60 and 57; 256 x
+        // 1,000,000: 504 and 497; 300 x 12,000: 36 and 27; 2,000 x 4,000: 41 and 37;
+        // 1,024 x 1,000,000: 1,660 and 1,490; 16,384 x 300,000: 7,742 and 7,753)
         p.kernel = KERNEL_QS;
         p.bq = q2b;
         p.qtiles = (b + p.bq - 1) / p.bq;
