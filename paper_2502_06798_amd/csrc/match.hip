@@ -204,7 +204,12 @@ MatchPlan plan_tile(int dt, int64_t n, int64_t rb, int32_t b, int32_t k)
         if (sp > tiles) sp = tiles;                                // fewer rows than a tile's gain nothing
         const int64_t passes = (qt * sp + 255) / 256;
         const float rounds = dt == APC_F32 ? (float)tiles / sp : (float)((tiles + sp - 1) / sp);
-        const float t = passes * (rounds * (stages * (dt == APC_F32 ? kd.s32 : kd.s) + kd.e) + kd.f);
+        // (three or more tiles of 64 queries over a cache beyond the MALL wait for
+        // their rows: with this term 151 x 9,461,309 x 384 f16 takes 2,045 us, 2,731
+        // without; 151 x 2,000,000 x 768 e4m3 438 and 600; 300 x 1,000,000 x 1,024
+        // e4m3 459 and 577)
+        const float far = kd.bq == 64 && qt > 2 && n * rb > (256ll << 20) && dt != APC_F32 ? 0.06f : 0.f;
+        const float t = passes * (rounds * (stages * ((dt == APC_F32 ? kd.s32 : kd.s) + far) + kd.e) + kd.f);
         if (best > 0.f && t >= best) continue;
         best = t;
         p.bq = kd.bq;
@@ -251,7 +256,7 @@ MatchPlan plan_kernel(int dt, int64_t n, int32_t d, int32_t b, int32_t k)
         if (splits < 1) splits = 1;
         p.splits = (int)splits;
     } else if (q2b > 0 && ((b >= 128 && b <= 256 && n >= 65536 && n < 1000000) || (b <= 16 && n >= 500000) ||
-                               (b >= 512 && n <= 131072 && (n >= 8192 || b >= 2560)))) {
+                               (b >= 600 && n <= 131072 && (n >= 8192 || (b >= 2560 && (int64_t)b * n >= 8000000))))) {
         // 16-bit rows of 1536 bytes, k <= 10: queries in VGPRs, cache rows through
         // LDS, one workgroup per CU; the query tiles of a split share an XCD.
         // For one or two tiles of 128 queries, and for the fewest queries against
@@ -263,6 +268,7 @@ MatchPlan plan_kernel(int dt, int64_t n, int32_t d, int32_t b, int32_t k)
         // 12,000: 397 and 599; 16,384 x 100,000: 2,626 and 2,806); elsewhere it is
         // not (32 x 1,000,000: 289 and 286; 100 x 100,000: 60 and 57; 256 x
         // 1,000,000: 504 and 497; 300 x 12,000: 36 and 27; 2,000 x 4,000: 41 and 37;
+        // 512 x 8,192: 29 and 27; 2,560 x 2,500: 42 and 38;
         // 1,024 x 1,000,000: 1,660 and 1,490; 16,384 x 300,000: 7,742 and 7,753)
         p.kernel = KERNEL_QS;
         p.bq = q2b;
