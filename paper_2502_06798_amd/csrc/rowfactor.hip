@@ -1,9 +1,9 @@
 // Row factors f = 1/|x| for cache entries (build) and queries (each batch).
 //
 // A group of lanes strides over a row in 16-byte chunks (coalesced), decodes to
-// float32, sums squares, then reduces in a fixed order so the result is
-// deterministic.  For e4m3fn rows the norm
-// is that of the codes: the positive row scale cancels in the cosine.
+// float32, sums squares, then reduces in a fixed order, the same for every
+// grouping, so the result is deterministic.  For e4m3fn rows the norm is that
+// of the codes: the positive row scale cancels in the cosine.
 #include "apc_internal.h"
 
 namespace apc {
@@ -55,9 +55,15 @@ __device__ inline void accum_chunk(const uint4 v, float& ss, bool& bad)
 // A group of G lanes per row (16, 32 or 64: the smallest with at most eight
 // units per lane), RPG rows per group at once, so that every wavefront has
 // several rows' loads in flight whatever the row size.  A wavefront per row of
-// 768 bytes had one load of 48 lanes in flight (1,000,000 rows: 461 us, 1.7
-// TB/s); now 137 us, 5.6 TB/s, near what plain reads reach.
-template <int DT, int G, int RPG>
+// 768 bytes had one load of 48 lanes in flight (1,000,000 e4m3 rows: 470 us, 1.6
+// TB/s); now 125 us, 6.2 TB/s, what plain reads reach.
+//
+// A row's sum does not depend on G, so the same row has the same factor bits in
+// a call of any size: unit u of 16 bytes always belongs to partial sum u % 64,
+// of which a lane keeps 64 / G, and the 64 are added in one order.  Rows of at
+// most A G units leave all but a lane's first A partial sums 0: those take no
+// registers (1,000,000 e4m3 rows of 256: 62 us, 69 with all four).
+template <int DT, int G, int RPG, int A = 64 / G>
 __global__ __launch_bounds__(256) void k_row_factors(const uint8_t* __restrict__ rows, int64_t n,
                                                       int64_t row_bytes, const float* __restrict__ scale,
                                                       const int32_t* __restrict__ slot_of_entry,
@@ -65,31 +71,44 @@ __global__ __launch_bounds__(256) void k_row_factors(const uint8_t* __restrict__
                                                       BuildStatus* __restrict__ st, uint8_t* __restrict__ rowflags)
 {
     constexpr int GPB = 256 / G;                          // groups per block
+    static_assert(A <= 64 / G, "a lane has 64 / G partial sums");
     const int gl = threadIdx.x % G;
     const int64_t r0 = ((int64_t)blockIdx.x * GPB + threadIdx.x / G) * RPG;
-    float ss[RPG];
+    float ss[RPG][A];
     bool bad[RPG];
 #pragma unroll
     for (int i = 0; i < RPG; ++i) {
-        ss[i] = 0.f;
+#pragma unroll
+        for (int a = 0; a < A; ++a) ss[i][a] = 0.f;
         bad[i] = false;
     }
-    for (int64_t off = (int64_t)gl * 16; off < row_bytes; off += G * 16) {
-        uint4 v[RPG];
+    for (int64_t off = (int64_t)gl * 16; off < row_bytes; off += 64 * 16) {
+        uint4 v[A][RPG];
 #pragma unroll
-        for (int i = 0; i < RPG; ++i) {
-            const int64_t r = r0 + i < n ? r0 + i : n - 1;
-            v[i] = *reinterpret_cast<const uint4*>(rows + r * row_bytes + off);
-        }
+        for (int a = 0; a < A; ++a)
+            if (off + a * G * 16 < row_bytes)
 #pragma unroll
-        for (int i = 0; i < RPG; ++i) accum_chunk<DT>(v[i], ss[i], bad[i]);
+                for (int i = 0; i < RPG; ++i) {
+                    const int64_t r = r0 + i < n ? r0 + i : n - 1;
+                    v[a][i] = *reinterpret_cast<const uint4*>(rows + r * row_bytes + off + a * G * 16);
+                }
+#pragma unroll
+        for (int a = 0; a < A; ++a)
+            if (off + a * G * 16 < row_bytes)
+#pragma unroll
+                for (int i = 0; i < RPG; ++i) accum_chunk<DT>(v[a][i], ss[i][a], bad[i]);
     }
 #pragma unroll
     for (int i = 0; i < RPG; ++i) {
-        // (a row's partial sums are added in a fixed order: by lane distance)
+        // partial sum p plus p ^ 32, then ^ 16, .. ^ 1: within a lane as far as
+        // it holds both, then by lane distance
+#pragma unroll
+        for (int m = 32 / G; m >= 1; m >>= 1)
+#pragma unroll
+            for (int a = 0; a < m && a + m < A; ++a) ss[i][a] += ss[i][a + m];
 #pragma unroll
         for (int m = G / 2; m >= 1; m >>= 1) {
-            ss[i] += __shfl_xor(ss[i], m, 64);
+            ss[i][0] += __shfl_xor(ss[i][0], m, 64);
             bad[i] |= (bool)__shfl_xor((int)bad[i], m, 64);
         }
     }
@@ -98,14 +117,15 @@ __global__ __launch_bounds__(256) void k_row_factors(const uint8_t* __restrict__
     for (int i = 0; i < RPG; ++i) {
         const int64_t r = r0 + i;
         if (r >= n) return;
+        const float sum = ss[i][0];
         uint32_t flags = 0;
-        if (bad[i] || !__builtin_isfinite(ss[i])) flags |= ST_NONFINITE;
-        else if (!(ss[i] > 0.f)) flags |= ST_ZERO;
+        if (bad[i] || !__builtin_isfinite(sum)) flags |= ST_NONFINITE;
+        else if (!(sum > 0.f)) flags |= ST_ZERO;
         if (scale) {
             float s = scale[r];
             if (!(__builtin_isfinite(s) && s > 0.f)) flags |= ST_SCALE;
         }
-        if (f) f[r] = flags ? __int_as_float(0x7fc00000) : 1.0f / __builtin_sqrtf(ss[i]);
+        if (f) f[r] = flags ? __int_as_float(0x7fc00000) : 1.0f / __builtin_sqrtf(sum);
         if (slot_of_entry) {
             int32_t v = slot_of_entry[r];
             if (v < -1 || (int64_t)v >= n_slots) flags |= ST_SLOT;
@@ -124,14 +144,20 @@ void run_row_factors(int64_t n, int64_t row_bytes, const uint8_t* r, const float
                      int64_t n_slots, float* f, BuildStatus* st, uint8_t* rowflags, hipStream_t s)
 {
     auto grid = [n](int64_t per) { return dim3((unsigned)((n + per - 1) / per)); };
-    if (n <= 2048)                                         // a batch of queries: every row's loads at once
-        k_row_factors<DT, 64, 1><<<grid(4), 256, 0, s>>>(r, n, row_bytes, scale, slots, n_slots, f, st, rowflags);
-    else if (row_bytes <= 8 * 16 * 16)
-        k_row_factors<DT, 16, 2><<<grid(32), 256, 0, s>>>(r, n, row_bytes, scale, slots, n_slots, f, st, rowflags);
-    else if (row_bytes <= 8 * 32 * 16)
-        k_row_factors<DT, 32, 2><<<grid(16), 256, 0, s>>>(r, n, row_bytes, scale, slots, n_slots, f, st, rowflags);
-    else
-        k_row_factors<DT, 64, 2><<<grid(8), 256, 0, s>>>(r, n, row_bytes, scale, slots, n_slots, f, st, rowflags);
+#define APC_RF(G, RPG, ...) \
+    k_row_factors<DT, G, RPG, ##__VA_ARGS__><<<grid(256 / G * RPG), 256, 0, s>>>(r, n, row_bytes, scale, slots, n_slots, f, st, rowflags)
+    // A batch of queries: every row's loads at once.  Wide rows that take little
+    // decoding have loads enough in flight with a wavefront per row (200,000 rows
+    // of 1,024 floats: 127 us, 138 with two rows per 32 lanes; 300,000 of 2,048
+    // bf16 192 and 206), e4m3 rows do not (1,000,000 of 768: 470 us, 125 with two
+    // per 16 lanes)
+    if (n <= 2048 || (DT != APC_E4M3 && row_bytes > (DT == APC_F32 ? 2048 : 3072))) APC_RF(64, 1);
+    else if (row_bytes <= 16 * 16) APC_RF(16, 2, 1);
+    else if (row_bytes <= 2 * 16 * 16) APC_RF(16, 2, 2);
+    else if (row_bytes <= 8 * 16 * 16) APC_RF(16, 2);
+    else if (row_bytes <= 8 * 32 * 16) APC_RF(32, 2);
+    else APC_RF(64, 2);
+#undef APC_RF
 }
 
 }  // namespace

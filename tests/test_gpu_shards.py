@@ -84,6 +84,53 @@ def test_sharded_match_equals_whole_cache(apc, dtype, cuts):
         c.close()
 
 
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 768), ("f32", 1100), ("f16", 8), ("f16", 384), ("f16", 768),
+                                     ("f16", 2056), ("bf16", 1024), ("bf16", 1544), ("e4m3", 768), ("e4m3", 1040), ("e4m3", 4112)])
+def test_row_factors_depend_on_the_row_alone(apc, dtype, d):
+    """The same rows in calls of few and of many rows (lanes per row and rows
+    per group differ): the same bits."""
+    say(f"row factors of parts {dtype} d={d}")
+    n = 6000
+    e, _ = make_rows(n, d, dtype, 31)
+    whole = torch.empty(n, device="cuda")
+    apc.apc_row_factors(e, whole)
+    for a, z in ((0, 1), (0, 2048), (1000, 3049), (17, 2066), (3500, 6000)):
+        part = torch.empty(z - a, device="cuda")
+        apc.apc_row_factors(e[a:z], part)
+        torch.cuda.synchronize()
+        assert torch.equal(part, whole[a:z]), f"rows {a}..{z}"
+
+
+@pytest.mark.parametrize("dtype,d", [("f16", 768), ("bf16", 384), ("f16", 1024), ("e4m3", 1536)])
+def test_small_shards_equal_whole_cache(apc, dtype, d):
+    """Shards of fewer and more than 2,048 rows, all of which hold much of every
+    top-k: whole cache and shards agree bit for bit, in the scores too."""
+    say(f"small shards {dtype} d={d}")
+    cuts, b, k = [0, 100, 1100, 3148, 4100, 8000], 200, 20
+    n = cuts[-1]
+    e, es = make_rows(n, d, dtype, 33, clusters=1)
+    q, qs = make_rows(b, d, dtype, 34)
+    whole = apc.apc_build_cache(e, es)
+    ts = torch.empty((b, k), device="cuda")
+    ti = torch.empty((b, k), dtype=torch.int32, device="cuda")
+    apc.apc_match_batch(whole, q, qs, k, ts, ti, apc.workspace_tensor(whole, b, k))
+    g = len(cuts) - 1
+    ls = torch.empty((g, b, k), device="cuda")
+    li = torch.empty((g, b, k), dtype=torch.int32, device="cuda")
+    for a in range(g):
+        c = apc.apc_build_cache(e[cuts[a]:cuts[a + 1]].contiguous(), None if es is None else es[cuts[a]:cuts[a + 1]].contiguous())
+        apc.apc_match_batch(c, q, qs, k, ls[a], li[a], apc.workspace_tensor(c, b, k))
+        torch.cuda.synchronize()
+        c.close()
+    ms = torch.empty((b, k), device="cuda")
+    mi = torch.empty((b, k), dtype=torch.int32, device="cuda")
+    apc.apc_merge_shards(ls, li, g, b, k, cuts[:-1], k, ms, mi)
+    torch.cuda.synchronize()
+    assert all((ti < c).any() and (ti >= c).any() for c in cuts[1:-1])     # every shard's side is in the lists
+    assert torch.equal(mi, ti) and torch.equal(ms, ts)
+    whole.close()
+
+
 def test_merge_shards_offsets_near_int32_limit(apc, orc):
     # global entry numbers are summed in 64 bits; those of 2^31 - 1 or more are
     # not candidates (they would wrap to negative int32 numbers)
