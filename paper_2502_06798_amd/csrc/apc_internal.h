@@ -89,8 +89,9 @@ hipError_t launch_qs8(const MatchPlan& p, int dt, int64_t n, int32_t d, const vo
                       hipStream_t s);
 
 // float32 caches of at most 512 blocks of 32 rows, d a multiple of 64, k <= 32,
-// b <= 48: one workgroup per 32-row block and 16-query tile, four wavefronts
-// over d (f32small.hip); writes the query factors to fq
+// b <= 48, or b <= 256 and at most 1,200 workgroups: one workgroup per 32-row
+// block and 16-query tile, eight wavefronts over d (four where d is not a
+// multiple of 128; f32small.hip); writes the query factors to fq
 bool f32s_fits(int dt, int64_t n, int32_t d, int32_t b, int32_t k);
 int f32s_queries();
 int f32s_rows();

@@ -26,9 +26,15 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int FS_QT = 16;      // queries per tile
 constexpr int FS_ROWS = 32;    // cache rows per workgroup
-// most queries: each tile of 16 reads the cache again (16 x 10,000 x 768: 21 us,
-// 45 with the tiled kernel; 100 x 10,000 x 768: 67 us and 47)
-constexpr int FS_MAXB = 48;
+// Each tile of 16 queries reads the cache again, so what the tiled kernel takes
+// for one tile of queries is reached at about 1,250 workgroups, whatever d (this
+// kernel and the tiled one, us, d = 768: 100 x 1,000 16.7 and 44.8; 256 x 2,000
+// 35 and 46; 96 x 5,000 36 and 45; 128 x 5,000 45.7 and 45.8; 96 x 10,000 60 and
+// 47; d = 384: 96 x 5,000 27 and 31, 128 x 5,000 32 and 31; d = 1,536: 100 x 1,000
+// 20 and 74).  Up to 48 queries it is ahead on its largest caches too
+// (48 x 16,384, k = 5: d = 256 24 and 28, d = 768 44 and 48; with k = 32 behind,
+// 63 and 54).
+constexpr int FS_MAXB = 256, FS_ANYB = 48, FS_MAXW = 1200;
 constexpr int FS_NONE = 0x7fffffff;
 
 __device__ inline float fs_clamp1(float x) { return __builtin_fminf(__builtin_fmaxf(x, -1.0f), 1.0f); }
@@ -166,8 +172,9 @@ __global__ __launch_bounds__(FS_NW * 64, 4) void k_f32s(const float* __restrict_
 
 bool f32s_fits(int dt, int64_t n, int32_t d, int32_t b, int32_t k)
 {
-    return dt == APC_F32 && d >= 64 && d % 64 == 0 && k >= 1 && k <= FS_ROWS && n >= 1 &&
-           (n + FS_ROWS - 1) / FS_ROWS <= 512 && b >= 1 && b <= FS_MAXB;
+    const int64_t blocks = (n + FS_ROWS - 1) / FS_ROWS, tiles = ((int64_t)b + FS_QT - 1) / FS_QT;
+    return dt == APC_F32 && d >= 64 && d % 64 == 0 && k >= 1 && k <= FS_ROWS && n >= 1 && blocks <= 512 && b >= 1 &&
+           b <= FS_MAXB && (b <= FS_ANYB || blocks * tiles <= FS_MAXW);
 }
 
 int f32s_queries() { return FS_QT; }

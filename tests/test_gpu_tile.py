@@ -84,7 +84,8 @@ def test_tile_edges(apc, dtype, b, n, d, k):
 @pytest.mark.parametrize("dtype,b,n,d,k", [
     ("f16", 16, 500000, 768, 10), ("f16", 17, 66000, 768, 10), ("bf16", 127, 65536, 768, 9), ("bf16", 128, 65536, 768, 10),
     ("f16", 256, 65537, 768, 1), ("f16", 256, 65537, 768, 11), ("f16", 257, 65537, 768, 10),      # query-stationary or tiled
-    ("f32", 48, 2000, 256, 5), ("f32", 49, 2000, 256, 5),                                         # small float32 or tiled
+    ("f32", 48, 2000, 256, 5), ("f32", 49, 2000, 256, 5), ("f32", 48, 16384, 256, 5), ("f32", 49, 16384, 256, 5),   # small float32 or tiled
+    ("f32", 256, 2400, 64, 32), ("f32", 256, 2401, 64, 32), ("f32", 257, 2000, 128, 9), ("f32", 60, 9600, 192, 1), ("f32", 65, 9600, 192, 1),
     ("e4m3", 12288, 20001, 512, 7), ("e4m3", 12288, 20000, 512, 7), ("f16", 4097, 20001, 256, 17),  # two wavefronts per SIMD or tiled
 ])
 def test_routes_meet(apc, dtype, b, n, d, k):
