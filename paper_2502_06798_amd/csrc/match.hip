@@ -222,7 +222,7 @@ MatchPlan plan_tile(int dt, int64_t n, int64_t rb, int32_t b, int32_t k)
     p.off_gt = align256(sizeof(float) * (size_t)p.b_pad);          // buckets
     // (the buckets are used where every one of the k gets rows: see tile_kernel.h)
     p.buckets = TL_CLASSES * p.splits >= k;
-    p.off_g2 = align256(p.off_gt + (p.buckets ? sizeof(int) * (size_t)p.b_pad * k : 0));   // log lengths
+    p.off_g2 = align256(p.off_gt + (p.buckets ? sizeof(int) * (size_t)p.b_pad * k * tile_ways(k, p.splits) : 0));   // log lengths
     p.off_ps = align256(p.off_g2 + sizeof(int) * lists);           // logs
     p.off_qp = align256(p.off_ps + sizeof(uint64_t) * lists * tile_log_cap(k));
     p.bytes = align256(p.off_qp + (size_t)(p.b_pad * copy));
@@ -346,6 +346,7 @@ hipError_t launch_match(const MatchPlan& p, int dt, int64_t n, int32_t d, const 
         a.qtiles = p.qtiles;
         a.cap = tile_log_cap(k);
         a.buckets = p.buckets;
+        a.ways = tile_ways(k, p.splits);
         // query tiles that share an L2 (4 MB): about half of it
         const int64_t fit = (2 << 20) / ((int64_t)a.nst * 64 * p.bq);
         a.group = fit < 2 ? 2 : fit > 32 ? 32 : (int32_t)fit;

@@ -12,11 +12,11 @@ struct TileArgs {
     int64_t fe_len;         // entry factors allocated (zeros past n)
     const uint8_t* qcopy;   // the queries in the kernel's load order (tile_copy_bytes)
     const float* fq;        // query factors (NaN: cannot be matched), b_pad
-    int* bucket;            // [k][b_pad] order-preserving keys of the shared maxima
+    int* bucket;            // [k][ways][b_pad] order-preserving keys of the shared maxima
     uint64_t* log;          // [b_pad][splits][cap] keys
     int32_t* cnt;           // [b_pad][splits]
     int64_t b_pad;
-    int32_t b, rb, k, nst, splits, qtiles, cap, buckets, group;
+    int32_t b, rb, k, nst, splits, qtiles, cap, buckets, ways, group;
 };
 
 hipError_t launch_tile_f32(int bq, const TileArgs& a, hipStream_t s);
@@ -37,6 +37,21 @@ inline int64_t tile_stages(int64_t row_bytes) { return row_bytes > 256 ? (row_by
 // classes of disjoint rows per split whose running maxima go into the buckets:
 // the two lane halves of each of a tile's eight 32-row blocks
 constexpr int TL_CLASSES = 16;
+// Parts of a bucket (its value is the largest of them), a power of two: the
+// classes of at most 16 splits meet in one part.  With one part, the atomics of
+// 256 splits on one to three addresses per query held up the kernel (32 x 57,558
+// x 1,024 f16: k = 1 46.8 us, 33.6 now; k = 2 58.5 and 34.8; k = 5 44.5 and 36.3;
+// 200 x 50,000 x 512, k = 2: 55.9 and 41.8; 64 x 200,000 x 512 bf16, k = 10: 65.0
+// and 61.0).  More parts take longer to read (1 x 300,000 x 768 e4m3, k = 3:
+// 51.1 us, 55.6 with 8 splits per part; 77 x 300,007 x 384 f16, k = 7: 69.1 and
+// 73.2), and parts where few splits meet are only prepared and read for nothing
+// (2,187 x 1,862 x 256 e4m3, k = 2, 7 splits: 26 us, 33 with eight parts).
+inline int tile_ways(int32_t k, int splits)
+{
+    int w = 1;
+    while (k * w * 16 < splits) w *= 2;
+    return w;
+}
 // places of a (query, split) log
 int tile_log_cap(int32_t k);
 

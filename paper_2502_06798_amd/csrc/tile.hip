@@ -65,7 +65,7 @@ __global__ __launch_bounds__(256) void k_tile_prep(const uint8_t* __restrict__ q
 // pair finds its rank by counting the larger keys (keys are unique), the k
 // best keep their places and their last becomes the bound.
 __global__ __launch_bounds__(TM_NT) void k_tile_merge(const uint64_t* __restrict__ log, const int32_t* __restrict__ cnt,
-                                                      const int* __restrict__ bucket, int use_buckets, int64_t b_pad,
+                                                      const int* __restrict__ bucket, int ways, int64_t b_pad,
                                                       int splits, int cap, int32_t k, const float* __restrict__ fq,
                                                       float* __restrict__ top_s, int32_t* __restrict__ top_i)
 {
@@ -87,8 +87,15 @@ __global__ __launch_bounds__(TM_NT) void k_tile_merge(const uint64_t* __restrict
     }
     __syncthreads();
     uint64_t least = 1;                                   // smallest key of interest
-    if (use_buckets) {
-        if (tid < k) atomicMin(&bound, bucket[(int64_t)tid * b_pad + q]);
+    if (ways) {                                           // 0: no buckets
+        if (tid < 64) {                                   // k ways <= 64: a bucket's parts in neighbouring lanes
+            int v = tid < k * ways ? bucket[(int64_t)tid * b_pad + q] : 0x7fffffff;
+            for (int w = 1; w < ways; w *= 2) {
+                const int o = __shfl_xor(v, w, 64);
+                v = o > v ? o : v;
+            }
+            if (tid < k * ways) atomicMin(&bound, v);
+        }
         __syncthreads();
         const int i = bound;
         const uint32_t u = (uint32_t)(i >= 0 ? i : i ^ 0x7fffffff);
@@ -174,7 +181,7 @@ hipError_t launch_tile_prep(int dt, const void* q, const float* q_scale, int32_t
 {
     const dim3 grid((unsigned)((a.b_pad + 3) / 4)), block(256);
     const uint8_t* qp = static_cast<const uint8_t*>(q);
-    const int64_t nb = a.buckets ? a.b_pad * a.k : 0;
+    const int64_t nb = a.buckets ? a.b_pad * a.k * a.ways : 0;
 #define APC_PREP(DT) k_tile_prep<DT><<<grid, block, 0, s>>>(qp, q_scale, b, a.b_pad, row_bytes, bq, a.nst, fq, qcopy, a.bucket, nb)
     switch (dt) {
     case APC_F32: APC_PREP(APC_F32); break;
@@ -198,7 +205,7 @@ hipError_t launch_tile(int dt, int bq, const TileArgs& a, hipStream_t s)
 
 hipError_t launch_tile_merge(const TileArgs& a, float* top_s, int32_t* top_i, hipStream_t s)
 {
-    k_tile_merge<<<(unsigned)a.b, TM_NT, 0, s>>>(a.log, a.cnt, a.bucket, a.buckets, a.b_pad, a.splits, a.cap, a.k, a.fq,
+    k_tile_merge<<<(unsigned)a.b, TM_NT, 0, s>>>(a.log, a.cnt, a.bucket, a.buckets ? a.ways : 0, a.b_pad, a.splits, a.cap, a.k, a.fq,
                                                  top_s, top_i);
     return hipGetLastError();
 }

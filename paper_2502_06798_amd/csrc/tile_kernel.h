@@ -27,7 +27,8 @@
 //  * all splits together: the lanes' running maxima (of disjoint rows, 16
 //    classes per workgroup) go into k buckets per query by atomic max, after
 //    tiles 1, 2, 4, 8, ..; the smallest bucket has k pairs at or above it.
-//    It is read during the next tile.  After the first tiles this is close to the
+//    A bucket is the largest of its parts (tile_ways), which keep the splits'
+//    atomics apart.  It is read during the next tile.  After the first tiles this is close to the
 //    k-th best of everything seen by all splits, so almost nothing passes;
 //  * a log that is full is cut to its k best, whose smallest is a bound too.
 // Any of them may lag: F then only lets more pairs through.  k_tile_merge takes
@@ -514,13 +515,24 @@ __global__ __launch_bounds__(TL_NT) void k_tile(const TileArgs A)
         // barriers that follow make the bounds visible before the filter)
         const bool fresh = A.buckets && it > 0 && (it & (it - 1)) == 0;
         auto refresh = [&]() __attribute__((always_inline)) {
+            constexpr int RU = BQ == 256 ? 4 : 8;                  // loads that go out together
+            const int parts = k * A.ways;
             for (int ql = tid; ql < BQ; ql += TL_NT) {
-                int mn = 0x7fffffff;
-#pragma unroll 8
-                for (int j = 0; j < k; ++j) {
-                    const int v = __hip_atomic_load(A.bucket + (int64_t)j * A.b_pad + q0 + ql, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-                    mn = v < mn ? v : mn;
+                int mn = 0x7fffffff, mx = (int)0x80000000;
+                for (int j0 = 0; j0 < parts; j0 += RU) {
+                    int v[RU];
+#pragma unroll
+                    for (int i = 0; i < RU; ++i)
+                        v[i] = __hip_atomic_load(A.bucket + (int64_t)(j0 + i < parts ? j0 + i : parts - 1) * A.b_pad + q0 + ql,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                    for (int i = 0; i < RU; ++i) {
+                        mx = v[i] > mx ? v[i] : mx;
+                        if (((j0 + i + 1) & (A.ways - 1)) == 0) {  // uniform: a bucket's last part
+                            if (j0 + i < parts) mn = mx < mn ? mx : mn;
+                            mx = (int)0x80000000;
+                        }
+                    }
                 }
                 const float F = q2_unkey(mn);
                 if (F > sm.f[ql]) sm.f[ql] = F;
@@ -667,12 +679,15 @@ __global__ __launch_bounds__(TL_NT) void k_tile(const TileArgs A)
                 const int ql = qloc(mq);
                 const float F = *(volatile float*)&sm.f[ql], fq = sm.fq[ql];
 #pragma unroll
-                for (int mb = 0; mb < ME; ++mb)
+                for (int mb = 0; mb < ME; ++mb) {
                     // (a query with a NaN factor logs nothing, whatever its bound)
-                    if (rm[mq][mb] > neg_inf() && clamp1(rm[mq][mb] * fq) > F)
-                        __hip_atomic_fetch_max(
-                            A.bucket + (int64_t)((split * TL_CLASSES + (we * ME + mb) * 2 + hl) % k) * A.b_pad + q0 + ql,
-                            q2_key(clamp1(rm[mq][mb] * fq)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (rm[mq][mb] > neg_inf() && clamp1(rm[mq][mb] * fq) > F) {
+                        const int c = split * TL_CLASSES + (we * ME + mb) * 2 + hl, g = c / k;
+                        const int part = (c - g * k) * A.ways + (g & (A.ways - 1));
+                        __hip_atomic_fetch_max(A.bucket + (int64_t)part * A.b_pad + q0 + ql, q2_key(clamp1(rm[mq][mb] * fq)),
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                }
             }
         }
     }

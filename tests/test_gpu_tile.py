@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from tests.gpu_check import say
+from tests.match_plan import TILE, plan
 
 pytestmark = pytest.mark.gpu
 
@@ -79,6 +80,20 @@ def test_tile_edges(apc, dtype, b, n, d, k):
     q, qs = rows(b, d, dtype, b + 7)
     ts, ti = match(apc, e, es, q, qs, k)
     check(e, q, k, ts, ti, {"f32": 1e-5, "e4m3": 1e-4}.get(dtype, 1e-5))
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 5, 9, 15])
+@pytest.mark.parametrize("dtype,b,n,d", [("f16", 40, 140001, 256), ("e4m3", 130, 70000, 640)])
+def test_tile_buckets_of_several_parts(apc, dtype, b, n, d, k):
+    """256 and 85 splits of several tiles: buckets of 16 parts to one."""
+    say(f"tile parts {dtype} b={b} n={n} d={d} k={k}")
+    p = plan(dtype, b, n, d, k)
+    assert p.kernel == TILE and p.tiles >= 3 and p.splits in (256, 85)
+    assert p.parts == ({1: 16, 2: 8, 3: 8, 5: 4, 9: 2, 15: 2} if p.splits == 256 else {1: 8, 2: 4, 3: 2, 5: 2, 9: 1, 15: 1})[k]
+    e, es = rows(n, d, dtype, n + k)
+    q, qs = rows(b, d, dtype, b + k)
+    ts, ti = match(apc, e, es, q, qs, k)
+    check(e, q, k, ts, ti, {"e4m3": 1e-4}.get(dtype, 1e-5))
 
 
 @pytest.mark.parametrize("dtype,b,n,d,k", [
