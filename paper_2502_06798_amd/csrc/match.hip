@@ -171,11 +171,16 @@ MatchPlan plan_tile(int dt, int64_t n, int64_t rb, int32_t b, int32_t k)
     p.kernel = KERNEL_TILE;
     // queries of one pass: the logs stay below 26 MB, the copy of the queries
     // below 5.8 MB unless 32 queries are longer
-    const int64_t copy = tile_stages(rb) * 64;
+    const int64_t copy = tile_stages(rb) * 64, tiles = (n + 255) / 256;
     int64_t chunk = (11 << 19) / copy / 256 * 256;
     if (chunk < 256) chunk = (11 << 19) / copy >= 128 ? 128 : (11 << 19) / copy >= 64 ? 64 : 32;
-    const int64_t most = k <= 16 ? 65536 : 32768;
-    if (chunk > most) chunk = most;
+    // Over a cache of few tiles the logs are few (a split has a tile at least),
+    // and passes of 5.8 MB of queries leave most of the chip idle: together at
+    // most 30 MB (float32: 5,916 x 1,318 x 1,536 in seven passes 611 us, in two
+    // 374; 2,000 x 300 x 1,536 228 and 79; 600 x 1,000 x 3,072 409 and 138; f16:
+    // 16,384 x 1,000 x 1,024 210 and 142)
+    const int64_t few = 30000000 / (copy + tiles * (8 * tile_log_cap(k) + 8) + 4 * k + 8) / 256 * 256;
+    if (few > chunk && few * tiles <= (k <= 16 ? 65536 : 32768)) chunk = few;
     // passes of equal size (a pass takes as long for a part of its queries)
     const int64_t passes_b = ((int64_t)b + chunk - 1) / chunk, unit = chunk < 256 ? chunk : 256;
     chunk = (((int64_t)b + passes_b - 1) / passes_b + unit - 1) / unit * unit;
@@ -194,7 +199,7 @@ MatchPlan plan_tile(int dt, int64_t n, int64_t rb, int32_t b, int32_t k)
                                                                     {128, 0.60f, 2.05f, 2.0f, 6.f},
                                                                     {64, 0.36f, 1.05f, 1.2f, 3.f},
                                                                     {32, 0.30f, 0.57f, 1.0f, 2.f}};
-    const int64_t tiles = (n + 255) / 256, stages = tile_stages(rb);
+    const int64_t stages = tile_stages(rb);
     float best = 0.f;
     for (const auto& kd : kinds) {
         if (kd.bq > 128 && k > 16) continue;                       // longer logs (tile_log_cap)

@@ -18,13 +18,14 @@ class _Plan(ctypes.Structure):
                 [(f, ctypes.c_size_t) for f in ("off_fq", "off_gt", "off_g2", "off_ps", "off_pi", "off_qp", "bytes")])
 
 
-Plan = collections.namedtuple("Plan", "kernel bq qtiles splits passes rows tiles bytes parts")
+Plan = collections.namedtuple("Plan", "kernel bq qtiles splits passes rows tiles bytes parts off_end")
 
 
 def plan(dtype, b, n, d, k):
     """kernel, queries per tile, tiles, splits, passes over the batch, rows of the
     largest split, tiles of 256 rows in it (k_tile), workspace bytes, parts of a
-    shared bucket (k_tile; 0: no buckets)."""
+    shared bucket (k_tile; 0: no buckets), the end of what the kernel uses of the
+    workspace."""
     f = apc.load()._ZN3apc10plan_matchEiliii
     f.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32]
     f.restype = _Plan
@@ -35,4 +36,6 @@ def plan(dtype, b, n, d, k):
     blocks = (n + 31) // 32
     rows = -(-blocks // p.splits) * 32
     parts = (p.off_g2 - p.off_gt) // (4 * p.b_pad * k) if p.kernel == TILE and p.buckets else 0
-    return Plan(p.kernel, p.bq, p.qtiles, p.splits, passes, rows, -(-rows // 256), p.bytes, parts)
+    stages = max(4, -(-d * SIZE[dtype] // 128) * 2)
+    return Plan(p.kernel, p.bq, p.qtiles, p.splits, passes, rows, -(-rows // 256), p.bytes, parts,
+                p.off_qp + p.b_pad * stages * 64 if p.kernel == TILE else p.bytes)

@@ -1,7 +1,10 @@
 """Which kernel a match is given to, and its tiles (host only: no GPU call)."""
+import math
+import random
+
 import pytest
 
-from tests.match_plan import F32S, KERNEL, TILE, plan
+from tests.match_plan import F32S, KERNEL, SIZE, TILE, plan
 
 
 @pytest.mark.parametrize("b,n,d,k", [(49, 1000, 1536, 5), (100, 1000, 768, 10), (256, 2000, 768, 10), (96, 5000, 384, 10),
@@ -24,3 +27,25 @@ def test_few_splits_meet_in_a_bucket(b, n, k):
     p = plan("f16", b, n, 640, k)
     assert p.kernel == TILE and p.splits <= 16 * k * p.parts and (p.parts == 1 or p.splits > 8 * k * p.parts)
     assert k * p.parts <= 64                              # a wavefront reads them
+
+
+@pytest.mark.parametrize("dtype,b,n,d,k,most", [("f32", 5916, 1318, 1536, 1, 2), ("f32", 2000, 300, 1536, 5, 1), ("f32", 600, 1000, 3072, 5, 1),
+                                                ("f32", 4000, 1000, 1024, 10, 1), ("f16", 16384, 1000, 1024, 10, 3), ("e4m3", 16384, 300, 256, 64, 1)])
+def test_few_rows_take_many_queries_per_pass(dtype, b, n, d, k, most):
+    """Passes of few queries over few rows leave most of the chip idle."""
+    p = plan(dtype, b, n, d, k)
+    assert p.kernel == TILE and p.passes <= most and p.qtiles * p.splits >= 64
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "e4m3"])
+def test_tiled_workspace_fits_the_static_array(dtype):
+    """Whatever the shape, unless 32 queries are longer than 5.8 MB or the lists of
+    the shape (b x k pairs and more) already pass it."""
+    rng = random.Random(4)
+    for _ in range(4000):
+        log = lambda lo, hi: int(math.exp(rng.uniform(math.log(lo), math.log(hi))))
+        d, b, n = log(1, 2500) * 16, log(1, 200000), log(1, 20000000)
+        k = min(n, rng.randint(1, 64))
+        p = plan(dtype, b, n, d, k)
+        if p.kernel == TILE and 32 * d * SIZE[dtype] < 5 << 20:
+            assert p.off_end <= 32 << 20, (dtype, b, n, d, k, p)
