@@ -234,24 +234,34 @@ MatchPlan plan_tile(int dt, int64_t n, int64_t rb, int32_t b, int32_t k)
     return p;
 }
 
+// Where the kernel of two wavefronts per SIMD with the queries in registers (no
+// query loads at all; rows of 512, 768 or 1024 bytes, k <= 32) is ahead of the
+// tiled one.  It reads the cache once per 256 queries from the L2, while the
+// tiled kernel also streams the queries; but its lists are slow to fill, so it
+// needs rows to pay for them, more of them the longer the lists, until the tiled
+// kernel's logs of 96 places cost as much (k > 16).  This kernel's time over the
+// tiled one's, geometric means over 900 random shapes, by query-row pairs b n:
+//   k = 1     1.1 at 1e8, 0.98 at 2.5e8, 0.88 at 1e9     k <= 3  1.0 at 5e8, 0.91 at 1e9
+//   k <= 6    1.1 at 5e8, 0.98 at 1.2e9                  k <= 11 1.08 at 1e9, 0.98 at 2.4e9
+//   k <= 16   1.1 at 6e8, 0.96 at 1e9                    k > 16  1.1 at 2e8, 0.93 at 5e8
+// for 8,192 queries and more with k >= 14 0.9 (0.74 to 1.1) from 6,000 rows on, and
+// for 12,288 queries and more 0.69 to 0.96 from 2,000 rows on.
+bool qs8_ahead(int64_t n, int64_t b, int32_t k)
+{
+    if (b >= 12288) return n >= 2000;
+    if (b >= 8192 && k >= 14 && n >= 6000) return true;
+    const int64_t pairs = k == 1 ? 250000000 : k <= 3 ? 500000000 : k <= 6 ? 1200000000ll : k <= 11 ? 2400000000ll
+                        : k <= 16 ? 1000000000ll : 400000000;
+    return b * n >= pairs && b >= (k <= 6 ? 1024 : 4096);
+}
+
 MatchPlan plan_kernel(int dt, int64_t n, int32_t d, int32_t b, int32_t k)
 {
     MatchPlan p{};
     const int64_t rb = (int64_t)d * elem_bytes(dt);
     const int q2b = qs_queries(dt, rb, k);
     const int q8b = qs8_queries(dt, rb, k);
-    // Two wavefronts per SIMD with the queries in registers (no query loads at
-    // all), where there are many queries and its lists, slow to fill, have
-    // rows enough to pay: it reads the cache once per 256 queries from the L2,
-    // while the tiled kernel also streams the queries.  Measured, this one
-    // against the tiled one: 16,384 x 300,000 x 768 e4m3 3.39 and 4.20 ms,
-    // 16,384 x 30,000 (k = 32) 0.87 and 1.31, 4,096 x 1,000,000 x 512 f16 4.28
-    // and 4.68, 8,192 x 300,000 x 512 f16 2.68 and 2.76, 6,000 x 40,000 x 768
-    // e4m3 (k = 32) 0.57 and 0.64; but 2,048 x 1,000,000 x 768 e4m3 (k = 32) 2.14
-    // and 1.99, 3,000 x 300,000 x 256 f16 0.70 and 0.57, 8,192 x 20,000 x 512
-    // f16 0.33 and 0.28, 512 x 1,000,000 x 768 e4m3 (k = 32) 0.84 and 0.56.
-    const bool many = b >= 12288 ? n > 20000 : b >= 4096 && ((int64_t)b * n >= 2400000000ll || (k > 16 && n > 20000));
-    if (q8b > 0 && many) {
+    if (q8b > 0 && qs8_ahead(n, b, k)) {
         p.kernel = KERNEL_QS8;
         p.bq = q8b;
         p.qtiles = (b + p.bq - 1) / p.bq;

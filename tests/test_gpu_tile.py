@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from tests.gpu_check import say
-from tests.match_plan import TILE, plan
+from tests.match_plan import KERNEL, SIZE, TILE, plan
 
 pytestmark = pytest.mark.gpu
 
@@ -111,6 +111,29 @@ def test_routes_meet(apc, dtype, b, n, d, k):
     ts, ti = match(apc, e, es, q, qs, k)
     r = torch.arange(0, b, max(1, b // 97), device="cuda")
     check(e, q[r], k, ts[r], ti[r], {"f32": 1e-5, "e4m3": 1e-4}.get(dtype, 1e-5))
+
+
+@pytest.mark.parametrize("dtype,d,k,first,second", [
+    # (b, n) whose kernel holds lists, and beside it (b, n) of the tiled one
+    ("e4m3", 512, 1, (5000, 50000), (5000, 49999)), ("f16", 384, 3, (1024, 488282), (1023, 488282)),
+    ("bf16", 256, 7, (12288, 2000), (12287, 2000)), ("f16", 384, 20, (8192, 6000), (8191, 6000)), ("e4m3", 1024, 16, (4096, 244141), (4095, 244141)),
+])
+def test_kernels_agree_where_they_meet(apc, dtype, d, k, first, second):
+    """Both sides of a line between the kernels: right, and where they have the
+    same rows, bit for bit the same lists."""
+    say(f"lines {dtype} d={d} k={k} {first} {second}")
+    assert [KERNEL[plan(dtype, b, n, d, k).kernel] for b, n in (first, second)] == ["k_qs" if d * SIZE[dtype] == 1536 else "k_qs8", "k_tile"]
+    e, es = rows(max(first[1], second[1]), d, dtype, d + k)
+    q, qs = rows(max(first[0], second[0]), d, dtype, d + k + 1)
+    got = []
+    for b, n in (first, second):
+        ts, ti = match(apc, e[:n].contiguous(), None if es is None else es[:n].contiguous(), q[:b].contiguous(), None if qs is None else qs[:b].contiguous(), k)
+        r = torch.arange(0, b, max(1, b // 97), device="cuda")
+        check(e[:n], q[r], k, ts[r], ti[r], {"e4m3": 1e-4}.get(dtype, 1e-5))
+        got.append((ts, ti))
+    b = min(first[0], second[0])
+    if first[1] == second[1]:
+        assert torch.equal(got[0][0][:b], got[1][0][:b]) and torch.equal(got[0][1][:b], got[1][1][:b])
 
 
 @pytest.mark.parametrize("b", [60, 150])

@@ -20,6 +20,19 @@ def test_other_float32_caches_are_tiled(b, n, d, k):
     assert KERNEL[plan("f32", b, n, d, k).kernel] == "k_tile"
 
 
+@pytest.mark.parametrize("kernel,dtype,b,n,d,k", [
+    # the tiled kernel took 1.1 to 1.5 times as long here
+    ("k_qs8", "e4m3", 4250, 434517, 512, 1), ("k_qs8", "bf16", 7894, 182636, 384, 2), ("k_qs8", "f16", 1401, 640566, 384, 2),
+    ("k_qs8", "e4m3", 15116, 6805, 768, 1), ("k_qs8", "e4m3", 14323, 5904, 768, 32), ("k_qs8", "f16", 13929, 3410, 384, 20),
+    ("k_qs8", "e4m3", 10991, 92492, 512, 16),
+    # and these it took as long or less
+    ("k_tile", "f16", 12, 130000, 768, 10), ("k_tile", "f16", 600, 500000, 768, 10), ("k_tile", "e4m3", 2048, 260000, 1536, 2), ("k_tile", "e4m3", 600, 9000, 768, 1),
+    ("k_tile", "f16", 6000, 100000, 512, 10), ("k_tile", "bf16", 3000, 6000, 512, 32),
+])
+def test_kernel_of_a_shape(kernel, dtype, b, n, d, k):
+    assert KERNEL[plan(dtype, b, n, d, k).kernel] == kernel
+
+
 @pytest.mark.parametrize("k", range(1, 17))
 @pytest.mark.parametrize("b,n", [(1, 300000), (32, 57558), (97, 15170), (200, 50000), (2000, 3000)])
 def test_few_splits_meet_in_a_bucket(b, n, k):
