@@ -36,6 +36,7 @@ MALL_BYTES = 256 << 20
 # code reports null.
 TRAFFIC_SOURCES = ("paper_2502_06798_amd/csrc/qs_kernel.h", "paper_2502_06798_amd/csrc/qs.hip",
                    "paper_2502_06798_amd/csrc/qs_f16.hip", "paper_2502_06798_amd/csrc/qs_bf16.hip",
+                   "paper_2502_06798_amd/csrc/qs_e4m3.hip",
                    "paper_2502_06798_amd/csrc/qs8_kernel.h",
                    "paper_2502_06798_amd/csrc/qs8_f16.hip", "paper_2502_06798_amd/csrc/qs8_bf16.hip",
                    "paper_2502_06798_amd/csrc/qs8_e4m3.hip", "paper_2502_06798_amd/csrc/match.hip")

@@ -255,6 +255,32 @@ bool qs8_ahead(int64_t n, int64_t b, int32_t k)
     return b * n >= pairs && b >= (k <= 6 ? 1024 : 4096);
 }
 
+// Where the kernel with the queries of a wavefront in registers (rows of 1536
+// bytes, k <= 10) is ahead of the tiled one.  Its lists are in registers: an
+// insertion costs a pass over the wavefront, so it is ahead for small k, where
+// few pairs are inserted, and for middling caches, over which the tiled kernel's
+// tiles of 256 rows divide unevenly (its 128-row groups lose less) or its prep
+// and merge weigh.  This kernel's time over the tiled one's, geometric means
+// over 1,500 random shapes (f16, bf16, e4m3), at rows n:
+//   b <= 64            k = 1, 2 0.80 to 1.0; k = 3 0.95 to 12,000, 1.0 to 1.15 beyond; k = 10 1.0 to 1.28
+//   b 65 to 512        k <= 3 0.74 to 1.0 (b > 128: 1.0 to 1.1 from 1,000,000); k = 5 1.05 below 4,000, 0.78 to 0.95, 1.03 from 500,000;
+//                      k = 7 1.1 below 8,000, 0.84 to 0.97; k = 10 1.2 below 8,000, 0.82 to 1.0 from
+//                      65,000 (b > 256: 16,000), 1.0 to 1.1 from 500,000
+//   b > 512            k = 1 0.63 to 0.95; k = 5 0.81 to 0.95 from 2,000; k = 10 1.15 at 1,000, 0.88 to 1.04
+//                      from 8,000 (b > 2,560: 4,000), 1.05 to 1.1 from 130,000 (e4m3: 60,000)
+bool qs_ahead(int dt, int64_t n, int64_t b, int32_t k)
+{
+    if (b > 512) {
+        const int64_t least = k <= 3 ? 0 : k <= 5 ? 2000 : k <= 7 ? 6000 : b >= 2560 ? 4000 : 8192;
+        return n >= least && n <= (dt == APC_E4M3 ? 60000 : 131072);
+    }
+    if (k >= 8) return n < 500000 && (b > 256 ? n >= 16000 : b >= 128 && n >= 65536);
+    if (k >= 6) return n < 500000 && b > 128 && n >= 12000;
+    if (k >= 4) return n < 500000 && b > 64 && n >= 4000;
+    if (k == 3 && b <= 64) return n <= 12000;
+    return b <= 128 || n < 1000000;
+}
+
 MatchPlan plan_kernel(int dt, int64_t n, int32_t d, int32_t b, int32_t k)
 {
     MatchPlan p{};
@@ -270,21 +296,9 @@ MatchPlan plan_kernel(int dt, int64_t n, int32_t d, int32_t b, int32_t k)
         if (splits > ngr) splits = ngr;
         if (splits < 1) splits = 1;
         p.splits = (int)splits;
-    } else if (q2b > 0 && ((b >= 128 && b <= 256 && n >= 65536 && n < 1000000) || (b <= 16 && n >= 500000) ||
-                               (b >= 600 && n <= 131072 && (n >= 8192 || (b >= 2560 && (int64_t)b * n >= 8000000))))) {
-        // 16-bit rows of 1536 bytes, k <= 10: queries in VGPRs, cache rows through
-        // LDS, one workgroup per CU; the query tiles of a split share an XCD.
-        // For one or two tiles of 128 queries, and for the fewest queries against
-        // a large cache, it is still ahead of the tiled kernel (256 x 100,000: 76
-        // us and 85; 200 x 200,000: 114 and 128; 128 x 100,000: 63 and 67; 1 x
-        // 1,000,000: 270 and 276; 4 x 1,000,000: 275 and 278), and for large
-        // batches against a small one (600 x 30,000: 57 and 68; 1,024 x 60,000: 128
-        // and 142; 2,639 x 5,728: 43 and 51; 8,192 x 1,000: 70 and 95; 16,384 x
-        // 12,000: 397 and 599; 16,384 x 100,000: 2,626 and 2,806); elsewhere it is
-        // not (32 x 1,000,000: 289 and 286; 100 x 100,000: 60 and 57; 256 x
-        // 1,000,000: 504 and 497; 300 x 12,000: 36 and 27; 2,000 x 4,000: 41 and 37;
-        // 512 x 8,192: 29 and 27; 2,560 x 2,500: 42 and 38;
-        // 1,024 x 1,000,000: 1,660 and 1,490; 16,384 x 300,000: 7,742 and 7,753)
+    } else if (q2b > 0 && qs_ahead(dt, n, b, k)) {
+        // queries in VGPRs, cache rows through LDS, one workgroup per CU; the query
+        // tiles of a split share an XCD
         p.kernel = KERNEL_QS;
         p.bq = q2b;
         p.qtiles = (b + p.bq - 1) / p.bq;

@@ -74,7 +74,7 @@ __global__ __launch_bounds__(256) void k_qprep(const uint8_t* __restrict__ qry, 
 
 int qs_queries(int dt, int64_t row_bytes, int k)
 {
-    return dt == APC_F16 || dt == APC_BF16 ? q2_queries(row_bytes, k) : 0;
+    return dt == APC_F16 || dt == APC_BF16 || dt == APC_E4M3 ? q2_queries(row_bytes, k) : 0;
 }
 
 int qs_group_rows() { return Q2_EB * 32; }
@@ -108,6 +108,7 @@ hipError_t launch_qs(const MatchPlan& p, int dt, int64_t n, int32_t d, const voi
     switch (dt) {
     case APC_F16: return launch_qs_f16(p, n, rb, emb, fe, q, fq, gthr, b, k, ps, pi, s);
     case APC_BF16: return launch_qs_bf16(p, n, rb, emb, fe, q, fq, gthr, b, k, ps, pi, s);
+    case APC_E4M3: return launch_qs_e4m3(p, n, rb, emb, fe, q, fq, gthr, b, k, ps, pi, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -1,4 +1,4 @@
-// Query-stationary similarity + exact top-k for 16-bit rows.
+// Query-stationary similarity + exact top-k for 16-bit and e4m3 rows.
 //
 // Grid: splits x query tiles.  A workgroup of four wavefronts (one per SIMD)
 // owns a tile of 4 x MQ x 32 queries and a contiguous range of cache entries
@@ -781,7 +781,7 @@ hipError_t run_qs(const MatchPlan& p, int64_t n, const void* emb, const float* f
 
 }  // namespace
 
-// The shape that is built: 16-bit rows of 1536 bytes, one block of 32 queries
+// The shape that is built: 16-bit or e4m3 rows of 1536 bytes, one block of 32 queries
 // per wavefront, lists of 10 slots, four 32-row blocks per stage and group.
 constexpr int Q2_RB = 1536, Q2_KR = 10, Q2_EB = 4;
 constexpr int q2_queries(int64_t row_bytes, int k) { return row_bytes == Q2_RB && k >= 1 && k <= Q2_KR ? Q2_NW * 32 : 0; }
@@ -798,4 +798,7 @@ hipError_t launch_qs_f16(const MatchPlan& p, int64_t n, int64_t rb, const void* 
                          const float* fq, int* gthr, int32_t b, int32_t k, float* ps, int* pi, hipStream_t s);
 hipError_t launch_qs_bf16(const MatchPlan& p, int64_t n, int64_t rb, const void* emb, const float* fe, const void* q,
                           const float* fq, int* gthr, int32_t b, int32_t k, float* ps, int* pi, hipStream_t s);
+hipError_t launch_qs_e4m3(const MatchPlan& p, int64_t n, int64_t rb, const void* emb, const float* fe, const void* q,
+                          const float* fq, int* gthr, int32_t b, int32_t k, float* ps, int* pi, hipStream_t s);
+
 }  // namespace apc
