@@ -262,7 +262,8 @@ bool qs8_ahead(int64_t n, int64_t b, int32_t k)
 // tiles of 256 rows divide unevenly (its 128-row groups lose less) or its prep
 // and merge weigh.  This kernel's time over the tiled one's, geometric means
 // over 1,500 random shapes (f16, bf16, e4m3), at rows n:
-//   b <= 64            k = 1, 2 0.80 to 1.0; k = 3 0.95 to 12,000, 1.0 to 1.15 beyond; k = 10 1.0 to 1.28
+//   b <= 64            k = 1, 2 0.80 to 1.0; k = 3 0.95 to 16,000, 1.0 to 1.15 beyond; k = 5 1.0 to 1.16 but
+//                      0.91 to 0.97 at 8,000 to 16,000; k = 10 1.0 to 1.28
 //   b 65 to 512        k <= 3 0.74 to 1.0 (b > 128: 1.0 to 1.1 from 1,000,000); k = 5 1.05 below 4,000, 0.78 to 0.95, 1.03 from 500,000;
 //                      k = 7 1.1 below 8,000, 0.84 to 0.97; k = 10 1.2 below 8,000, 0.82 to 1.0 from
 //                      65,000 (b > 256: 16,000), 1.0 to 1.1 from 500,000
@@ -276,8 +277,8 @@ bool qs_ahead(int dt, int64_t n, int64_t b, int32_t k)
     }
     if (k >= 8) return n < 500000 && (b > 256 ? n >= 16000 : b >= 128 && n >= 65536);
     if (k >= 6) return n < 500000 && b > 128 && n >= 12000;
-    if (k >= 4) return n < 500000 && b > 64 && n >= 4000;
-    if (k == 3 && b <= 64) return n <= 12000;
+    if (k >= 4) return b > 64 ? n >= 4000 && n < 500000 : n >= 8000 && n <= 16000;
+    if (k == 3 && b <= 64) return n <= 16000;
     return b <= 128 || n < 1000000;
 }
 

@@ -117,7 +117,7 @@ def test_routes_meet(apc, dtype, b, n, d, k):
     # (b, n) whose kernel holds lists, and beside it (b, n) of the tiled one
     ("e4m3", 512, 1, (5000, 50000), (5000, 49999)), ("f16", 384, 3, (1024, 488282), (1023, 488282)),
     ("bf16", 256, 7, (12288, 2000), (12287, 2000)), ("f16", 384, 20, (8192, 6000), (8191, 6000)), ("e4m3", 1024, 16, (4096, 244141), (4095, 244141)),
-    ("e4m3", 1536, 3, (64, 12000), (64, 12001)), ("bf16", 768, 5, (65, 4000), (64, 4000)), ("f16", 768, 7, (129, 12000), (128, 12000)),
+    ("e4m3", 1536, 3, (64, 16000), (64, 16001)), ("f16", 768, 5, (20, 8000), (20, 7999)), ("bf16", 768, 5, (65, 4000), (64, 4000)), ("f16", 768, 7, (129, 12000), (128, 12000)),
     ("e4m3", 1536, 10, (257, 16000), (256, 16000)), ("f16", 768, 10, (128, 65536), (127, 65536)), ("f16", 768, 2, (513, 131072), (513, 131073)),
     ("e4m3", 1536, 8, (600, 60000), (600, 60001)), ("bf16", 768, 10, (2560, 4000), (2559, 4000)), ("bf16", 768, 4, (513, 2000), (513, 1999)),
 ])

@@ -25,7 +25,7 @@ def test_other_float32_caches_are_tiled(b, n, d, k):
     ("k_qs8", "e4m3", 4250, 434517, 512, 1), ("k_qs8", "bf16", 7894, 182636, 384, 2), ("k_qs8", "f16", 1401, 640566, 384, 2),
     ("k_qs8", "e4m3", 15116, 6805, 768, 1), ("k_qs8", "e4m3", 14323, 5904, 768, 32), ("k_qs8", "f16", 13929, 3410, 384, 20),
     ("k_qs8", "e4m3", 10991, 92492, 512, 16),
-    ("k_qs", "e4m3", 80, 145030, 1536, 2), ("k_qs", "f16", 54, 15577, 768, 1), ("k_qs", "f16", 237, 18384, 768, 2), ("k_qs", "bf16", 13, 88611, 768, 1),
+    ("k_qs", "e4m3", 80, 145030, 1536, 2), ("k_qs", "f16", 54, 15577, 768, 1), ("k_qs", "f16", 237, 18384, 768, 2), ("k_qs", "bf16", 13, 88611, 768, 1), ("k_qs", "f16", 54, 15577, 768, 3),
     ("k_qs", "f16", 446, 136863, 768, 10), ("k_qs", "f16", 50, 197590, 768, 2), ("k_qs", "e4m3", 5065, 6702, 1536, 1), ("k_qs", "bf16", 300, 32000, 768, 10),
     # and these it took as long or less
     ("k_tile", "f16", 12, 130000, 768, 10), ("k_tile", "f16", 600, 500000, 768, 10), ("k_tile", "e4m3", 2048, 260000, 1536, 2), ("k_tile", "e4m3", 600, 9000, 768, 1),
