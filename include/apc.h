@@ -159,7 +159,9 @@ apc_status apc_validate_rows(apc_dtype dt, int64_t n, int32_t d, const void* row
 /* Copies the handle's n entry factors to out (n float32, device). */
 apc_status apc_cache_row_factors(const apc_cache* c, float* out, void* stream);
 
-/* Workspace bytes apc_match_batch needs for b queries and k neighbours. */
+/* Workspace bytes apc_match_batch needs for b queries and k neighbours.  Never
+   falls as b grows: a workspace for the largest batch serves every smaller one
+   with the same cache and k. */
 apc_status apc_match_workspace(const apc_cache* c, int32_t b, int32_t k, size_t* bytes /* host */);
 
 /*
@@ -189,9 +191,9 @@ apc_status apc_match_batch(const apc_cache* c, const void* q, const float* q_sca
  * of APC_STATIC_WS_BYTES that each device holds from the library's first
  * use on it until the process ends (looked up on the first call on a
  * device).  The call allocates nothing.  Same arguments, outputs and errors
- * as apc_match_batch, plus APC_E_WORKSPACE when apc_match_workspace(c, b, k)
- * exceeds APC_STATIC_WS_BYTES (every workload up to 16,384 queries x k = 32
- * fits).  Nothing in the array needs to start at zero.  All calls on one
+ * as apc_match_batch, plus APC_E_WORKSPACE when this batch needs more than
+ * APC_STATIC_WS_BYTES (never where apc_match_workspace(c, b, k) is within it;
+ * every workload up to 16,384 queries x k = 32 fits).  Nothing in the array needs to start at zero.  All calls on one
  * device share the array: calls that overlap on one device (other streams,
  * other threads) race and give undefined results; serialise them.
  */

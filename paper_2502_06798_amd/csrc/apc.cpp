@@ -290,7 +290,7 @@ apc_status apc_match_workspace(const apc_cache* c, int32_t b, int32_t k, size_t*
     if (b < 0) return fail(APC_E_ARG, "apc_match_workspace: b < 0");
     if (k < 1 || k > APC_MAX_K || k > c->n)
         return fail(APC_E_ARG, "apc_match_workspace: need 1 <= k <= min(n, %d) (k=%d)", APC_MAX_K, k);
-    *bytes = b == 0 ? 0 : apc::plan_match(c->dt, c->n, c->d, b, k).bytes;
+    *bytes = b == 0 ? 0 : apc::match_workspace(c->dt, c->n, c->d, b, k);
     return ok();
 }
 
@@ -310,9 +310,10 @@ apc_status apc_match_batch(const apc_cache* c, const void* q, const float* q_sca
     if (!top_score || !top_idx || !aligned16(top_score) || !aligned16(top_idx))
         return fail(APC_E_ARG, "apc_match_batch: outputs must be 16-byte aligned device pointers");
     const apc::MatchPlan p = apc::plan_match(c->dt, c->n, c->d, b, k);
-    if (!ws || ws_bytes < p.bytes || (reinterpret_cast<uintptr_t>(ws) & 255u))
+    const size_t need = apc::match_workspace(c->dt, c->n, c->d, b, k);
+    if (!ws || ws_bytes < need || (reinterpret_cast<uintptr_t>(ws) & 255u))
         return fail(APC_E_WORKSPACE, "apc_match_batch: workspace needs %zu bytes, 256-byte aligned (got %zu)",
-                    p.bytes, ws_bytes);
+                    need, ws_bytes);
     hipEvent_t ev0 = g_ev_start, ev1 = g_ev_stop;
     g_ev_start = g_ev_stop = nullptr;
     hipError_t e = apc::launch_match(p, c->dt, c->n, c->d, c->emb, c->fe, q, q_scale, b, k, top_score,

@@ -57,6 +57,8 @@ struct MatchPlan {
     size_t off_fq, off_gt, off_g2, off_ps, off_pi, off_qp, bytes;   // workspace layout
 };
 MatchPlan plan_match(int dt, int64_t n, int32_t d, int32_t b, int32_t k);
+// workspace that every batch of b or fewer fits in: never falls as b grows
+size_t match_workspace(int dt, int64_t n, int32_t d, int32_t b, int32_t k);
 
 // ev_start/ev_stop (may be null) are recorded around the similarity kernel.
 hipError_t launch_match(const MatchPlan& p, int dt, int64_t n, int32_t d, const void* emb,

@@ -145,10 +145,13 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 namespace {
 
 // The workspace of a plan with one list of k pairs for every (query, split),
-// by shape: what apc_match_workspace has always asked at least, so that a
-// caller with a workspace of a fixed size (apc_match_batch_static) is refused
-// exactly the batches beyond it, whichever kernel serves them.
-size_t list_bytes(int dt, int64_t n, int64_t rb, int32_t b, int32_t k)
+// by shape.  It covers k_qs, k_qs8 and k_f32s, and every plan asks at least this
+// much, so that apc_match_batch_static refuses the same batches whichever
+// kernel serves them: those whose lists (or, for rows that k_qs or k_qs8 is
+// built for, lists and queries) pass the static array.  (No plan of the tiled
+// kernel passes it by itself unless 32 of its queries are longer than 5.8 MB.)
+// most: the largest for a batch of b or fewer.
+size_t list_bytes(int dt, int64_t n, int64_t rb, int64_t b, int32_t k, bool most)
 {
     const bool stationary = dt != APC_F32 && k <= 32 && (rb == 512 || rb == 768 || rb == 1024 || rb == 1536);
     const bool eight = stationary && rb != 1536 && b > 256;
@@ -160,17 +163,24 @@ size_t list_bytes(int dt, int64_t n, int64_t rb, int32_t b, int32_t k)
     const int64_t target = stationary || k > 16 ? 256 : 512;
     int64_t splits = small ? parts : stationary ? (qt >= target ? 1 : target / qt) : (target + qt - 1) / qt;
     if (splits > parts) splits = parts;
-    const size_t bp = (size_t)(qt * bq), lists = bp * (size_t)splits;
-    return 2 * align256(4 * bp) + align256(eight ? 4 * lists : 0) + 2 * align256(4 * lists * k) +
-           align256(stationary ? bp * (size_t)rb : 0);
+    int64_t pairs = qt * splits;                                   // (query tile, split)
+    if (most && !small) {
+        // fewer tiles may have more splits each, up to the target between them all
+        // (one short of a tile more where splits are rounded up)
+        const int64_t bound = (target > qt ? target : qt) + (stationary ? 0 : qt - 1);
+        pairs = bound < qt * parts ? bound : qt * parts;
+    }
+    const size_t bp = (size_t)(qt * bq), lists = (size_t)(pairs * bq);
+    const size_t bytes = 2 * align256(4 * bp) + align256(eight ? 4 * lists : 0) + 2 * align256(4 * lists * k) +
+                         align256(stationary ? bp * (size_t)rb : 0);
+    const size_t below = most && b > 256 ? list_bytes(dt, n, rb, 256, k, true) : 0;   // (another shape up to 256 queries)
+    return bytes > below ? bytes : below;
 }
 
-MatchPlan plan_tile(int dt, int64_t n, int64_t rb, int32_t b, int32_t k)
+// Most queries of a pass of the tiled kernel: the logs stay below 26 MB, the copy
+// of the queries below 5.8 MB unless 32 queries are longer.
+int64_t tile_pass(int64_t n, int64_t rb, int32_t k)
 {
-    MatchPlan p{};
-    p.kernel = KERNEL_TILE;
-    // queries of one pass: the logs stay below 26 MB, the copy of the queries
-    // below 5.8 MB unless 32 queries are longer
     const int64_t copy = tile_stages(rb) * 64, tiles = (n + 255) / 256;
     int64_t chunk = (11 << 19) / copy / 256 * 256;
     if (chunk < 256) chunk = (11 << 19) / copy >= 128 ? 128 : (11 << 19) / copy >= 64 ? 64 : 32;
@@ -180,7 +190,40 @@ MatchPlan plan_tile(int dt, int64_t n, int64_t rb, int32_t b, int32_t k)
     // 374; 2,000 x 300 x 1,536 228 and 79; 600 x 1,000 x 3,072 409 and 138; f16:
     // 16,384 x 1,000 x 1,024 210 and 142)
     const int64_t few = 30000000 / (copy + tiles * (8 * tile_log_cap(k) + 8) + 4 * k + 8) / 256 * 256;
-    if (few > chunk && few * tiles <= (k <= 16 ? 65536 : 32768)) chunk = few;
+    return few > chunk && few * tiles <= (k <= 16 ? 65536 : 32768) ? few : chunk;
+}
+
+// tiles of 256 queries have no room for the longer logs of k > 16 (tile_log_cap)
+bool tile_takes(int bq, int64_t pass, int32_t k) { return (bq <= 128 || k <= 16) && bq <= pass; }
+
+// The most that a plan of the tiled kernel asks for a batch of b or fewer.  A
+// tile of bq queries is never the best for bq / 2 queries or fewer, and the
+// splits of all query tiles are 256 in all, or one each.
+size_t tile_bytes_most(int64_t n, int64_t rb, int64_t b, int32_t k)
+{
+    const int64_t pass = tile_pass(n, rb, k), copy = tile_stages(rb) * 64, tiles = (n + 255) / 256;
+    const int64_t bc = b < pass ? b : pass;
+    size_t bytes = 0;
+    for (int bq = 32; bq <= 256; bq *= 2) {
+        if (!tile_takes(bq, pass, k) || (bq > 32 && b <= bq / 2)) continue;
+        const int64_t qt = (bc + bq - 1) / bq, bound = qt > 256 ? qt : 256, pairs = bound < qt * tiles ? bound : qt * tiles;
+        const size_t bp = (size_t)(qt * bq), lists = (size_t)(pairs * bq);
+        // (parts of a bucket: k parts below an eighth of the splits, see tile_ways)
+        const size_t buckets = bp * k > lists / 8 ? bp * k : lists / 8;
+        const size_t t = align256(4 * bp) + align256(4 * buckets) + align256(4 * lists) + align256(8 * lists * tile_log_cap(k)) +
+                         align256(bp * copy);
+        if (t > bytes) bytes = t;
+    }
+    return bytes;
+}
+
+MatchPlan plan_tile(int dt, int64_t n, int64_t rb, int32_t b, int32_t k)
+{
+    MatchPlan p{};
+    p.kernel = KERNEL_TILE;
+    const int64_t copy = tile_stages(rb) * 64, tiles = (n + 255) / 256;
+    int64_t chunk = tile_pass(n, rb, k);
+    const int64_t pass = chunk;
     // passes of equal size (a pass takes as long for a part of its queries)
     const int64_t passes_b = ((int64_t)b + chunk - 1) / chunk, unit = chunk < 256 ? chunk : 256;
     chunk = (((int64_t)b + passes_b - 1) / passes_b + unit - 1) / unit * unit;
@@ -202,8 +245,7 @@ MatchPlan plan_tile(int dt, int64_t n, int64_t rb, int32_t b, int32_t k)
     const int64_t stages = tile_stages(rb);
     float best = 0.f;
     for (const auto& kd : kinds) {
-        if (kd.bq > 128 && k > 16) continue;                       // longer logs (tile_log_cap)
-        if (kd.bq > chunk) continue;
+        if (!tile_takes(kd.bq, pass, k)) continue;
         const int64_t qt = (bc + kd.bq - 1) / kd.bq;
         int64_t sp = qt >= 256 ? 1 : 256 / qt;
         if (sp > tiles) sp = tiles;                                // fewer rows than a tile's gain nothing
@@ -340,9 +382,18 @@ MatchPlan plan_kernel(int dt, int64_t n, int32_t d, int32_t b, int32_t k)
 MatchPlan plan_match(int dt, int64_t n, int32_t d, int32_t b, int32_t k)
 {
     MatchPlan p = plan_kernel(dt, n, d, b, k);
-    const size_t least = list_bytes(dt, n, (int64_t)d * elem_bytes(dt), b, k);
+    const size_t least = list_bytes(dt, n, (int64_t)d * elem_bytes(dt), b, k, false);
     if (p.bytes < least) p.bytes = least;
     return p;
+}
+
+size_t match_workspace(int dt, int64_t n, int32_t d, int32_t b, int32_t k)
+{
+    const int64_t rb = (int64_t)d * elem_bytes(dt);
+    const size_t lists = list_bytes(dt, n, rb, b, k, true);
+    if (f32s_fits(dt, n, d, b, k)) return lists;                   // and so does every smaller batch
+    const size_t tile = tile_bytes_most(n, rb, b, k);
+    return tile > lists ? tile : lists;
 }
 
 hipError_t launch_match(const MatchPlan& p, int dt, int64_t n, int32_t d, const void* emb,

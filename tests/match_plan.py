@@ -39,3 +39,11 @@ def plan(dtype, b, n, d, k):
     stages = max(4, -(-d * SIZE[dtype] // 128) * 2)
     return Plan(p.kernel, p.bq, p.qtiles, p.splits, passes, rows, -(-rows // 256), p.bytes, parts,
                 p.off_qp + p.b_pad * stages * 64 if p.kernel == TILE else p.bytes)
+
+
+def workspace(dtype, b, n, d, k):
+    """What apc_match_workspace asks for a batch of b."""
+    f = apc.load()._ZN3apc15match_workspaceEiliii
+    f.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32]
+    f.restype = ctypes.c_size_t
+    return f(DT[dtype], n, d, b, k)

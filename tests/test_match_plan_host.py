@@ -4,7 +4,7 @@ import random
 
 import pytest
 
-from tests.match_plan import F32S, KERNEL, SIZE, TILE, plan
+from tests.match_plan import F32S, KERNEL, SIZE, TILE, plan, workspace
 
 
 @pytest.mark.parametrize("b,n,d,k", [(49, 1000, 1536, 5), (100, 1000, 768, 10), (256, 2000, 768, 10), (96, 5000, 384, 10),
@@ -64,3 +64,29 @@ def test_tiled_workspace_fits_the_static_array(dtype):
         p = plan(dtype, b, n, d, k)
         if p.kernel == TILE and 32 * d * SIZE[dtype] < 5 << 20:
             assert p.off_end <= 32 << 20, (dtype, b, n, d, k, p)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16", "e4m3"])
+def test_workspace_never_falls_as_the_batch_grows(dtype):
+    """A workspace for the largest batch serves the smaller ones, and what a batch
+    is asked covers its plan, and is at most 36 MiB or twice what it or a
+    smaller one uses."""
+    rng = random.Random(6)
+    log = lambda lo, hi: int(math.exp(rng.uniform(math.log(lo), math.log(hi))))
+    for _ in range(1500):
+        d = rng.choice([256, 384, 512, 768, 1024, 1536, log(1, 2500) * 16])
+        n = log(1, 20000000)
+        k = min(n, rng.choice([1, 3, 10, 16, 17, 32, 33, 64]))
+        last, used = 0, 0
+        for b in sorted({log(1, 50000) for _ in range(24)} | {16, 17, 48, 49, 64, 65, 127, 128, 256, 257, 512, 513, 1023, 1024}):
+            ask, need = workspace(dtype, b, n, d, k), plan(dtype, b, n, d, k).bytes
+            used = max(used, need)
+            assert ask >= last and ask >= need, (dtype, b, n, d, k, last, ask, need)
+            last = ask
+        assert last <= max(36 << 20, 2 * used), (dtype, n, d, k, last, used)
+
+
+def test_workspace_of_the_shapes_that_fell():
+    """127 queries were asked 8.6 times what 128 were, and so on."""
+    for dtype, d, n, k, small, large in (("f16", 768, 300000, 5, 127, 128), ("f16", 256, 300000, 10, 2000, 8192), ("f32", 1024, 200000, 5, 256, 257)):
+        assert workspace(dtype, small, n, d, k) <= workspace(dtype, large, n, d, k)
