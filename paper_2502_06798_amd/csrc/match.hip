@@ -179,18 +179,26 @@ size_t list_bytes(int dt, int64_t n, int64_t rb, int64_t b, int32_t k, bool most
 
 // Most queries of a pass of the tiled kernel: the logs stay below 26 MB, the copy
 // of the queries below 5.8 MB unless 32 queries are longer.
-int64_t tile_pass(int64_t n, int64_t rb, int32_t k)
+int64_t tile_pass(int64_t rb)
+{
+    const int64_t copy = tile_stages(rb) * 64, pass = (11 << 19) / copy / 256 * 256;
+    return pass >= 256 ? pass : (11 << 19) / copy >= 128 ? 128 : (11 << 19) / copy >= 64 ? 64 : 32;
+}
+
+// The same over a cache of few tiles, whose logs are few (a split has a tile at
+// least): logs and copy below 30 MB together.  0: no more than tile_pass.
+int64_t tile_pass_few(int64_t n, int64_t rb, int32_t k)
 {
     const int64_t copy = tile_stages(rb) * 64, tiles = (n + 255) / 256;
-    int64_t chunk = (11 << 19) / copy / 256 * 256;
-    if (chunk < 256) chunk = (11 << 19) / copy >= 128 ? 128 : (11 << 19) / copy >= 64 ? 64 : 32;
-    // Over a cache of few tiles the logs are few (a split has a tile at least),
-    // and passes of 5.8 MB of queries leave most of the chip idle: together at
-    // most 30 MB (float32: 5,916 x 1,318 x 1,536 in seven passes 611 us, in two
-    // 374; 2,000 x 300 x 1,536 228 and 79; 600 x 1,000 x 3,072 409 and 138; f16:
-    // 16,384 x 1,000 x 1,024 210 and 142)
     const int64_t few = 30000000 / (copy + tiles * (8 * tile_log_cap(k) + 8) + 4 * k + 8) / 256 * 256;
-    return few > chunk && few * tiles <= (k <= 16 ? 65536 : 32768) ? few : chunk;
+    return few > tile_pass(rb) && few * tiles <= (k <= 16 ? 65536 : 32768) ? few : 0;
+}
+
+// passes of equal size (a pass takes as long for a part of its queries)
+int64_t tile_even(int64_t b, int64_t pass)
+{
+    const int64_t passes = (b + pass - 1) / pass, unit = pass < 256 ? pass : 256;
+    return ((b + passes - 1) / passes + unit - 1) / unit * unit;
 }
 
 // tiles of 256 queries have no room for the longer logs of k > 16 (tile_log_cap)
@@ -201,7 +209,8 @@ bool tile_takes(int bq, int64_t pass, int32_t k) { return (bq <= 128 || k <= 16)
 // splits of all query tiles are 256 in all, or one each.
 size_t tile_bytes_most(int64_t n, int64_t rb, int64_t b, int32_t k)
 {
-    const int64_t pass = tile_pass(n, rb, k), copy = tile_stages(rb) * 64, tiles = (n + 255) / 256;
+    const int64_t few = tile_pass_few(n, rb, k), pass = few ? few : tile_pass(rb);
+    const int64_t copy = tile_stages(rb) * 64, tiles = (n + 255) / 256;
     const int64_t bc = b < pass ? b : pass;
     size_t bytes = 0;
     for (int bq = 32; bq <= 256; bq *= 2) {
@@ -222,11 +231,17 @@ MatchPlan plan_tile(int dt, int64_t n, int64_t rb, int32_t b, int32_t k)
     MatchPlan p{};
     p.kernel = KERNEL_TILE;
     const int64_t copy = tile_stages(rb) * 64, tiles = (n + 255) / 256;
-    int64_t chunk = tile_pass(n, rb, k);
-    const int64_t pass = chunk;
-    // passes of equal size (a pass takes as long for a part of its queries)
-    const int64_t passes_b = ((int64_t)b + chunk - 1) / chunk, unit = chunk < 256 ? chunk : 256;
-    chunk = (((int64_t)b + passes_b - 1) / passes_b + unit - 1) / unit * unit;
+    int64_t pass = tile_pass(rb), chunk = tile_even(b, pass);
+    // Where such passes leave a quarter of the chip idle (128 queries and one tile
+    // to a workgroup) and larger ones fit: float32 5,916 x 1,318 x 1,536 in seven
+    // passes 611 us, in two 374; 2,000 x 300 x 1,536 228 and 79; 600 x 1,000 x 3,072
+    // 409 and 138; f16 16,384 x 1,000 x 1,024 210 and 142; e4m3 16,384 x 1,000 x 768
+    // 122 and 96.  Elsewhere they are as fast or faster (6,196 x 4,000 x 1,536 bf16:
+    // 182 us in four passes, 224 in two).
+    if (const int64_t few = tile_pass_few(n, rb, k); few && b > chunk && chunk / 128 * tiles < 192) {
+        pass = few;
+        chunk = tile_even(b, pass);
+    }
     const int64_t bc = b < chunk ? b : chunk;
     p.chunk = (int)chunk;
     // The tile that takes the least time by this model: a workgroup goes

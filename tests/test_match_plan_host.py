@@ -52,6 +52,11 @@ def test_few_rows_take_many_queries_per_pass(dtype, b, n, d, k, most):
     assert p.kernel == TILE and p.passes <= most and p.qtiles * p.splits >= 64
 
 
+@pytest.mark.parametrize("dtype,b,n,d,k,passes", [("bf16", 6196, 4000, 1536, 11, 4), ("f16", 4167, 5141, 1536, 2, 3)])
+def test_passes_that_fill_the_chip_stay_small(dtype, b, n, d, k, passes):
+    assert plan(dtype, b, n, d, k).passes == passes
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f16", "e4m3"])
 def test_tiled_workspace_fits_the_static_array(dtype):
     """Whatever the shape, unless 32 queries are longer than 5.8 MB or the lists of
