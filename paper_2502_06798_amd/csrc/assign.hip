@@ -124,14 +124,14 @@ __global__ __launch_bounds__(NT) void k_assign(const AssignTable targ, const flo
         }
 }
 
-// The same with every query's state in registers (thread tid owns queries
-// tid + c NTB, c < QPT): no global-memory round trip per round.  The block
-// is sized to the batch (NTB threads).  Each chunk of a round takes two
-// barriers: after the per-wave ballots, and after the ranks, which read the
-// level counts of the round so far (used[cur]) while threads p <= L write the
-// counts after this chunk into the other buffer.  The rounds stop once a round
-// has no applicant (every query placed; later rounds would change nothing).
-template <int QPT, int NTB>
+// The same for up to NTB queries, thread tid's query in its registers: no
+// global-memory round trip per round.  The block is sized to the batch.  Each
+// round takes two barriers: after the per-wave ballots, and after the ranks,
+// which read the level counts of the rounds before (used[cur]) while threads
+// p <= L write the counts after this round into the other buffer.  The rounds
+// stop once one has no applicant (every query placed; later rounds would change
+// nothing).
+template <int NTB>
 __global__ __launch_bounds__(NTB) void k_assign_reg(const AssignTable targ, const float* __restrict__ top_score,
                                                     int32_t ld, int32_t b, int32_t* __restrict__ opt_level,
                                                     int32_t* __restrict__ out_level,
@@ -144,93 +144,65 @@ __global__ __launch_bounds__(NTB) void k_assign_reg(const AssignTable targ, cons
     __shared__ int wcnt[NWAVE][APC_MAX_LEVELS + 2];          // [L + 1]: the wave has an applicant
     __shared__ AssignTable t;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    float best[QPT];
-#pragma unroll
-    for (int c = 0; c < QPT; ++c) {                          // issued before the table copy
-        const int q = c * NT + tid;
-        best[c] = q < b ? top_score[(int64_t)q * ld] : 0.f;
-    }
+    const bool mine = tid < b;
+    const float best = mine ? top_score[(int64_t)tid * ld] : 0.f;   // issued before the table copy
     table_to_lds<NT>(targ, t, tid);
     const int L = t.L;
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    int lam[QPT], lev[QPT], rk[QPT];
-#pragma unroll
-    for (int c = 0; c < QPT; ++c) {
-        const int q = c * NT + tid;
-        lam[c] = 0;
-        lev[c] = -1;
-        rk[c] = -1;
-        if (q < b)
-            for (int l = 0; l < L; ++l) lam[c] += best[c] >= t.theta[l];
-    }
+    int lam = 0, lev = -1, rk = -1;
+    if (mine)
+        for (int l = 0; l < L; ++l) lam += best >= t.theta[l];
     if (tid <= L) used[0][tid] = 0;
     int cur = 0;
-    const int nchunk = (b + NT - 1) / NT;
     for (int r = 0; r <= L; ++r) {
-        bool round_any = false;
+        int want = -1;
+        if (mine && lev < 0) want = r <= lam ? lam - r : r;
+        int pre = 0;
+        for (int p = 0; p <= L; ++p) {
+            const uint64_t m = __ballot(want == p);
+            if (want == p) pre = __popcll(m & lt_mask);
+            if (lane == 0) wcnt[wave][p] = __popcll(m);
+        }
+        const bool wave_any = __ballot(want >= 0) != 0;
+        if (lane == 0) wcnt[wave][L + 1] = wave_any;
+        __syncthreads();
+        bool any = false;
 #pragma unroll
-        for (int c = 0; c < QPT; ++c) {
-            if (c < nchunk) {                                 // uniform
-                const int q = c * NT + tid;
-                int want = -1;
-                if (q < b && lev[c] < 0) want = r <= lam[c] ? lam[c] - r : r;
-                int pre = 0;
-                for (int p = 0; p <= L; ++p) {
-                    const uint64_t m = __ballot(want == p);
-                    if (want == p) pre = __popcll(m & lt_mask);
-                    if (lane == 0) wcnt[wave][p] = __popcll(m);
-                }
-                const bool wave_any = __ballot(want >= 0) != 0;
-                if (lane == 0) wcnt[wave][L + 1] = wave_any;
-                __syncthreads();
-                bool any = false;
+        for (int w = 0; w < NWAVE; ++w) any |= wcnt[w][L + 1] != 0;
+        if (!any) break;                                      // uniform: no applicant
+        if (want >= 0) {
+            int rank = used[cur][want] + pre;
 #pragma unroll
-                for (int w = 0; w < NWAVE; ++w) any |= wcnt[w][L + 1] != 0;
-                if (!any) {                                   // uniform: no applicant in this chunk
-                    __syncthreads();                          // before the next chunk rewrites wcnt
-                    continue;
-                }
-                round_any = true;
-                if (want >= 0) {
-                    int rank = used[cur][want] + pre;
-#pragma unroll
-                    for (int w = 0; w < NWAVE; ++w) rank += w < wave ? wcnt[w][want] : 0;
-                    if (rank < t.level_cap[want]) {
-                        lev[c] = want;
-                        rk[c] = rank;
-                    }
-                }
-                if (tid <= L) {
-                    int tot = used[cur][tid];
-#pragma unroll
-                    for (int w = 0; w < NWAVE; ++w) tot += wcnt[w][tid];
-                    const int cap = t.level_cap[tid];
-                    used[cur ^ 1][tid] = tot < cap ? tot : cap;
-                }
-                __syncthreads();
-                cur ^= 1;
+            for (int w = 0; w < NWAVE; ++w) rank += w < wave ? wcnt[w][want] : 0;
+            if (rank < t.level_cap[want]) {
+                lev = want;
+                rk = rank;
             }
         }
-        if (!round_any) break;                                // uniform
-    }
+        if (tid <= L) {
+            int tot = used[cur][tid];
 #pragma unroll
-    for (int c = 0; c < QPT; ++c) {
-        const int q = c * NT + tid;
-        if (q >= b) continue;
-        const int p = lev[c];
+            for (int w = 0; w < NWAVE; ++w) tot += wcnt[w][tid];
+            const int cap = t.level_cap[tid];
+            used[cur ^ 1][tid] = tot < cap ? tot : cap;
+        }
+        __syncthreads();
+        cur ^= 1;
+    }
+    if (mine) {
         int inst = -1, slot = -1;
-        if (p >= 0) {
-            for (int j = t.level_first[p]; j < t.level_first[p + 1]; ++j)
-                if (rk[c] < t.ord_cum[j] + t.ord_cap[j]) {
+        if (lev >= 0) {
+            for (int j = t.level_first[lev]; j < t.level_first[lev + 1]; ++j)
+                if (rk < t.ord_cum[j] + t.ord_cap[j]) {
                     inst = t.ord_inst[j];
-                    slot = rk[c] - t.ord_cum[j];
+                    slot = rk - t.ord_cum[j];
                     break;
                 }
         }
-        opt_level[q] = lam[c];
-        out_level[q] = p;
-        out_inst[q] = inst;
-        out_slot[q] = slot;
+        opt_level[tid] = lam;
+        out_level[tid] = lev;
+        out_inst[tid] = inst;
+        out_slot[tid] = slot;
     }
     for (int p = 0; p <= L; ++p)
         for (int j = t.level_first[p] + tid; j < t.level_first[p + 1]; j += NT) {
@@ -335,6 +307,7 @@ __device__ inline void rank_levels(Ranks<QPT, NTB>& rk, const int (&v)[QPT], int
 template <int QPT, int NTB>
 __device__ inline void rounds_flow(const Ranks<QPT, NTB>& rk, const uint8_t* lam, const AssignTable& t, int lane, int* x)
 {
+    static_assert(QPT > 1, "reads the counts before each segment, which rank_levels leaves only for several queries per thread");
     constexpr int NSEG = Ranks<QPT, NTB>::NSEG;
     const int L = t.L, n = L + 1;
     int done = 0;                                                  // of this level's queries
@@ -475,18 +448,18 @@ __global__ __launch_bounds__(NTB) void k_assign_plan(const AssignTable targ, con
         for (int c = 0; c < QPT; ++c)
             lam[c] += lam[c] >= 0 && best[c] >= th;
     }
-    if (MODE == PLAN_ROUNDS) {
+    if constexpr (MODE == PLAN_ROUNDS) {
 #pragma unroll
         for (int c = 0; c < QPT; ++c) lams[c * NT + tid] = (uint8_t)lam[c];   // 255 past the batch
     }
     // Pass 1: rank among the queries of the same level; the histogram.
     rank_levels<QPT, NTB>(rkl, lam, n, tid, rs);
     // The plan.
-    if (MODE == PLAN_ROUNDS) {
+    if constexpr (MODE == PLAN_ROUNDS) {
         for (int e = tid; e < n * n; e += NT) xs[e] = 0;
         __syncthreads();
         if (tid < 64) rounds_flow<QPT, NTB>(rkl, lams, t, tid, xs);
-    } else if (MODE == PLAN_OPTIMAL) {
+    } else if constexpr (MODE == PLAN_OPTIMAL) {
         if (tid <= L) plan_level_own(L, rkl.total, t.level_cap, tid, w);
         __syncthreads();
         if (tid < L) plan_level_flow(L, tid, w);
@@ -618,11 +591,16 @@ hipError_t launch_plan_t(const AssignTable& t, const float* top_score, int32_t l
                          int32_t* opt_level, int32_t* out_level, int32_t* out_inst, int32_t* out_slot,
                          int32_t* inst_fill, hipStream_t s)
 {
-    if (b <= 256)
-        k_assign_plan<1, 256, MODE><<<1, 256, 0, s>>>(t, top_score, ld, b, plan, opt_level, out_level, out_inst, out_slot, inst_fill);
-    else if (b <= NT)
-        k_assign_plan<1, NT, MODE><<<1, NT, 0, s>>>(t, top_score, ld, b, plan, opt_level, out_level, out_inst, out_slot, inst_fill);
-    else if (b <= 4 * NT)
+    if constexpr (MODE != PLAN_ROUNDS) {                     // (up to NT queries the rounds have k_assign_reg)
+        if (b <= NT) {
+            if (b <= 256)
+                k_assign_plan<1, 256, MODE><<<1, 256, 0, s>>>(t, top_score, ld, b, plan, opt_level, out_level, out_inst, out_slot, inst_fill);
+            else
+                k_assign_plan<1, NT, MODE><<<1, NT, 0, s>>>(t, top_score, ld, b, plan, opt_level, out_level, out_inst, out_slot, inst_fill);
+            return hipGetLastError();
+        }
+    }
+    if (b <= 4 * NT)
         k_assign_plan<4, NT, MODE><<<1, NT, 0, s>>>(t, top_score, ld, b, plan, opt_level, out_level, out_inst, out_slot, inst_fill);
     else if (b <= 16 * NT)
         k_assign_plan<16, NT, MODE><<<1, NT, 0, s>>>(t, top_score, ld, b, plan, opt_level, out_level, out_inst, out_slot, inst_fill);
@@ -638,9 +616,9 @@ hipError_t launch_assign(const AssignTable& t, const float* top_score, int32_t l
                          int32_t* out_slot, int32_t* inst_fill, hipStream_t s)
 {
     if (b <= 256)
-        k_assign_reg<1, 256><<<1, 256, 0, s>>>(t, top_score, ld, b, opt_level, out_level, out_inst, out_slot, inst_fill);
+        k_assign_reg<256><<<1, 256, 0, s>>>(t, top_score, ld, b, opt_level, out_level, out_inst, out_slot, inst_fill);
     else if (b <= NT)
-        k_assign_reg<1, NT><<<1, NT, 0, s>>>(t, top_score, ld, b, opt_level, out_level, out_inst, out_slot, inst_fill);
+        k_assign_reg<NT><<<1, NT, 0, s>>>(t, top_score, ld, b, opt_level, out_level, out_inst, out_slot, inst_fill);
     else if (b <= 16 * NT)                               // several queries per thread: the rounds as a plan
         return launch_plan_t<PLAN_ROUNDS>(t, top_score, ld, b, nullptr, opt_level, out_level, out_inst, out_slot,
                                           inst_fill, s);

@@ -117,44 +117,40 @@ __global__ __launch_bounds__(TM_NT) void k_tile_merge(const uint64_t* __restrict
         if (tid == 0) m = c < k ? c : k;
         __syncthreads();
     };
-    // thread t reads the places t / splits, t / splits + per, .. of log
-    // t % splits (a log's entries are few: each thread's loads go out together)
-    const int per = splits >= TM_NT ? 1 : TM_NT / splits;
-    const int rounds = (splits + TM_NT - 1) / TM_NT;      // 1 unless there are more splits than threads
-    for (int r = 0; r < rounds; ++r) {
-        const int sp = r * TM_NT + tid % (splits < TM_NT ? splits : TM_NT);
-        const int sub = splits < TM_NT ? tid / splits : 0;
-        const bool mine = sp < splits && sub < per;
-        const int c = mine ? cnt[q * splits + sp] : 0;
-        const uint64_t* lg = log + (q * splits + (mine ? sp : 0)) * cap;
-        if (tid == 0) most = 0;
-        __syncthreads();
-        if (mine && sub == 0) atomicMax(&most, c);
-        __syncthreads();
-        const int end = most;
-        for (int p0 = 0; p0 < end; p0 += TM_UNROLL * per) {
-            uint64_t v[TM_UNROLL];
+    // (at most a thread per log.)  Thread t reads the places t / splits,
+    // t / splits + per, .. of log t % splits (a log's entries are few: each thread's
+    // loads go out together)
+    const int per = TM_NT / splits, sp = tid % splits, sub = tid / splits;
+    const bool mine = sub < per;
+    const int c = mine ? cnt[q * splits + sp] : 0;
+    const uint64_t* lg = log + (q * splits + sp) * cap;
+    if (tid == 0) most = 0;
+    __syncthreads();
+    if (mine && sub == 0) atomicMax(&most, c);
+    __syncthreads();
+    const int end = most;
+    for (int p0 = 0; p0 < end; p0 += TM_UNROLL * per) {
+        uint64_t v[TM_UNROLL];
 #pragma unroll
-            for (int i = 0; i < TM_UNROLL; ++i) {
-                const int at = p0 + i * per + sub;
-                v[i] = at < c ? lg[at] : 0;
+        for (int i = 0; i < TM_UNROLL; ++i) {
+            const int at = p0 + i * per + sub;
+            v[i] = at < c ? lg[at] : 0;
+        }
+#pragma unroll
+        for (int i = 0; i < TM_UNROLL; ++i) {
+            const bool in = v[i] >= least;
+            const uint64_t mask = __builtin_amdgcn_ballot_w64(in);
+            if (mask) {
+                int at = 0;
+                if (lane == 0) at = atomicAdd(&m, __builtin_popcountll(mask));
+                at = __builtin_amdgcn_readfirstlane(at);
+                if (in) buf[cur][at + __builtin_popcountll(mask & ((1ull << lane) - 1ull))] = v[i];
             }
-#pragma unroll
-            for (int i = 0; i < TM_UNROLL; ++i) {
-                const bool in = v[i] >= least;
-                const uint64_t mask = __builtin_amdgcn_ballot_w64(in);
-                if (mask) {
-                    int at = 0;
-                    if (lane == 0) at = atomicAdd(&m, __builtin_popcountll(mask));
-                    at = __builtin_amdgcn_readfirstlane(at);
-                    if (in) buf[cur][at + __builtin_popcountll(mask & ((1ull << lane) - 1ull))] = v[i];
-                }
-                if (i % 2 == 1) {                         // room for two more batches after every cut
-                    __syncthreads();
-                    const bool full = m > TM_BUF - 2 * TM_NT;
-                    __syncthreads();
-                    if (full) cut();
-                }
+            if (i % 2 == 1) {                             // room for two more batches after every cut
+                __syncthreads();
+                const bool full = m > TM_BUF - 2 * TM_NT;
+                __syncthreads();
+                if (full) cut();
             }
         }
     }
@@ -205,6 +201,7 @@ hipError_t launch_tile(int dt, int bq, const TileArgs& a, hipStream_t s)
 
 hipError_t launch_tile_merge(const TileArgs& a, float* top_s, int32_t* top_i, hipStream_t s)
 {
+    if (a.splits > TM_NT) return hipErrorInvalidValue;             // (plans have at most 256)
     k_tile_merge<<<(unsigned)a.b, TM_NT, 0, s>>>(a.log, a.cnt, a.bucket, a.buckets ? a.ways : 0, a.b_pad, a.splits, a.cap, a.k, a.fq,
                                                  top_s, top_i);
     return hipGetLastError();
