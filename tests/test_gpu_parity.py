@@ -126,49 +126,47 @@ CASES = [
     ("e4m3", 200, 1500, 112, 7),
     ("f16", 300, 129, 64, 64),
     # float32 caches of at most 512 blocks of 32 rows (d a multiple of 64,
-    # k <= 32, b <= 256): a workgroup per block, d over its wavefronts; a
-    # partial last block, one query, the largest cache, k = 32, partial and
-    # many query tiles
+    # k <= 32, b <= 48, or <= 256 and at most 1,200 workgroups): a workgroup per
+    # block, d over its wavefronts; a partial last block, one query, the largest
+    # cache, k = 32, partial and many query tiles
     ("f32", 16, 5000, 768, 5),
     ("f32", 1, 33, 128, 1),
     ("f32", 17, 16384, 256, 32),
     ("f32", 256, 2000, 64, 12),
     ("f32", 40, 70, 1024, 7),
     ("f32", 3, 1, 64, 1),              # a one-row cache
-    ("f32", 256, 16384, 64, 32),       # the largest batch, cache and k together
-    # streaming kernel: larger float caches, and 16-bit or e4m3 rows of sizes
-    # the query-stationary kernel is not built for (whole groups of 4 x 128
-    # bytes, 6 x 128 for e4m3), or k > 32
+    ("f32", 256, 16384, 64, 32),       # too many workgroups: tiled
+    # larger float32 caches, wide rows: the tiled kernel
     ("f32", 16, 20000, 768, 5),
     ("f16", 64, 1000, 1536, 12),
-    # query-stationary kernel: 16-bit or e4m3 rows of 512, 768, 1024 or 1536
-    # bytes, k <= 32; every shape family (rows, query blocks, 32-row blocks per
-    # group, lists of 10, 16 or 32 slots in registers or LDS)
-    ("e4m3", 100, 2050, 768, 10),      # 768 B, two query blocks, 10-slot lists
-    ("f16", 256, 7777, 768, 10),       # 1536 B, one block, four 32-row blocks
-    ("bf16", 3, 17, 256, 17),          # one group, one split
+    # rows of 512, 768, 1024 and 1536 bytes, for which there are kernels with lists
+    # (test_gpu_tile.py asserts which shapes they have) beside the tiled one: k and
+    # the numbers of queries and rows on either side of their lists' lengths, groups
+    # and tiles
+    ("f16", 256, 7777, 768, 10),
+    ("bf16", 3, 17, 256, 17),
     ("f16", 5, 40, 256, 3),
-    ("e4m3", 7, 33, 768, 33),          # k > 32: streaming
-    ("bf16", 100, 3000, 768, 20),      # 1536 B, 32-slot lists, two 32-row blocks
+    ("e4m3", 7, 33, 768, 33),
+    ("bf16", 100, 3000, 768, 20),
     ("f16", 256, 50000, 768, 10),
     ("bf16", 129, 3001, 768, 16),
     ("e4m3", 300, 9000, 768, 10),
     ("f16", 1, 31, 768, 5),
-    ("f16", 40, 100, 512, 7),          # 1024 B, lists in LDS
-    ("e4m3", 5, 70000, 512, 16),       # 512 B, two query blocks, 16-slot lists
+    ("f16", 40, 100, 512, 7),
+    ("e4m3", 5, 70000, 512, 16),
     ("bf16", 512, 20000, 256, 8),
     ("f16", 200, 40000, 256, 3),
-    ("f16", 150, 6000, 256, 12),       # 512 B, two query blocks
-    ("f16", 150, 6000, 256, 24),       # 512 B, one block, 32-slot lists
-    ("bf16", 70, 5000, 384, 16),       # 768 B, two query blocks
-    ("f16", 90, 5000, 512, 9),         # 1024 B, two query blocks, lists in LDS
-    ("e4m3", 90, 5000, 1024, 20),      # 1024 B e4m3, one block, 32-slot lists
-    ("e4m3", 33, 4000, 1536, 11),      # 1536 B e4m3, one block, four 32-row blocks
-    ("bf16", 64, 3000, 768, 29),       # 1536 B, 32-slot lists
-    ("e4m3", 40, 5000, 1536, 6),       # 1536 B e4m3, 10-slot lists
-    ("e4m3", 70, 6000, 1024, 10),      # 1024 B e4m3, two query blocks, 10-slot lists in LDS
-    ("f16", 80, 5000, 512, 14),        # 1024 B, 16-slot lists in LDS
-    ("f16", 130, 9000, 768, 11),       # 1536 B, 16-slot lists just above 10
+    ("f16", 150, 6000, 256, 12),
+    ("f16", 150, 6000, 256, 24),
+    ("bf16", 70, 5000, 384, 16),
+    ("f16", 90, 5000, 512, 9),
+    ("e4m3", 90, 5000, 1024, 20),
+    ("e4m3", 33, 4000, 1536, 11),
+    ("bf16", 64, 3000, 768, 29),
+    ("e4m3", 40, 5000, 1536, 6),
+    ("e4m3", 70, 6000, 1024, 10),
+    ("f16", 80, 5000, 512, 14),
+    ("f16", 130, 9000, 768, 11),
 ]
 
 
@@ -227,21 +225,21 @@ def test_match_many_groups_per_split(apc, orc, dtype, b, n, d, k):
     c.close()
 
 
-# Batches above 256 queries with 512-, 768- or 1024-byte rows go to the kernel with
-# two wavefronts per SIMD (256 queries per workgroup, lists in LDS): every row
-# type, both list sizes (k <= 16 and k <= 32), k = 1 and k = 32, a last group
-# of fewer than 64 rows, a cache smaller than one group, wavefronts without
-# queries (b just above a multiple of 32 and of 256) and many splits.
+# Batches above 256 queries of 512-, 768- and 1024-byte rows, which the kernel with
+# two wavefronts per SIMD is built for: it has the largest of them (test_gpu_tile.py
+# asserts which), the tiled kernel the others.  Every row type, k = 1 to 32, a last
+# group of fewer than 64 rows, a cache smaller than one group, b just above a
+# multiple of 32 and of 256, and many splits.
 QS8_CASES = [
     ("e4m3", 257, 5000, 768, 10),
-    ("e4m3", 300, 63, 512, 32),        # fewer rows than one group
+    ("e4m3", 300, 63, 512, 32),        # fewer rows than a group or tile
     ("e4m3", 1000, 20011, 512, 1),
-    ("f16", 513, 9000, 384, 16),       # 768-byte f16 rows
-    ("bf16", 700, 12345, 256, 17),     # 512-byte bf16 rows, 32-slot lists
+    ("f16", 513, 9000, 384, 16),
+    ("bf16", 700, 12345, 256, 17),
     ("f16", 2080, 30001, 256, 32),
     ("bf16", 1024, 7000, 384, 5),
     ("e4m3", 4099, 40000, 768, 32),
-    ("f16", 1030, 20001, 512, 16),     # 1024-byte rows: fragments read one step ahead
+    ("f16", 1030, 20001, 512, 16),
     ("bf16", 600, 9000, 512, 32),
     ("e4m3", 777, 15000, 1024, 20),
 ]
@@ -249,7 +247,7 @@ QS8_CASES = [
 
 @pytest.mark.parametrize("dtype,b,n,d,k", QS8_CASES)
 def test_match_two_waves_per_simd(apc, orc, dtype, b, n, d, k):
-    say(f"match (two wavefronts per SIMD) {dtype} b={b} n={n} d={d} k={k}")
+    say(f"match (two-wavefront widths) {dtype} b={b} n={n} d={d} k={k}")
     e, es = make_rows(n, d, dtype, 50 + n, clusters=max(1, n // 60))
     q, qs = make_rows(b, d, dtype, 60 + b, clusters=None)
     q[: b // 2] = e[torch.arange(b // 2, device="cuda") * 11 % n]
@@ -275,11 +273,11 @@ def test_match_two_waves_per_simd(apc, orc, dtype, b, n, d, k):
 
 
 @pytest.mark.parametrize("dtype,d,b,n,k", [
-    ("f16", 64, 3, 1000, 20),        # tiled / streaming kernels
+    ("f16", 64, 3, 1000, 20),        # tiled kernel
     ("f32", 64, 3, 1000, 20),        # small float32 caches, four wavefronts over d
     ("f32", 768, 17, 5000, 32),      # the same, eight wavefronts
-    ("f16", 768, 5, 3000, 10),       # query-stationary kernel (1536-byte rows)
-    ("e4m3", 768, 300, 2000, 32),    # two wavefronts per SIMD (768-byte rows)
+    ("f16", 768, 5, 3000, 10),       # tiled kernel, 1536-byte rows
+    ("e4m3", 768, 300, 2000, 32),    # tiled kernel, 768-byte rows
 ])
 def test_match_ties_take_lower_index(apc, orc, dtype, d, b, n, k):
     """Every cache row the same: every score ties, and the top-k is entries
@@ -299,7 +297,7 @@ def test_match_ties_take_lower_index(apc, orc, dtype, d, b, n, k):
     c.close()
 
 
-@pytest.mark.parametrize("dtype,d", [("f16", 32), ("f16", 256), ("f32", 64)])   # tiled, streaming, small float32
+@pytest.mark.parametrize("dtype,d", [("f16", 32), ("f16", 256), ("f32", 64)])   # tiled, small float32
 def test_match_invalid_query_rows(apc, dtype, d):
     say(f"match invalid query rows {dtype} d={d}")
     e, _ = make_rows(500, d, dtype, 5)

@@ -1,7 +1,10 @@
 """The tiled similarity kernel at the sizes where it can go wrong: every query
-tile (32, 64, 128, 256 queries), rows that end inside a stage of 64 bytes or a
-slot of 128, splits whose last tile is partial or a single row, k at the edges
-of its bounds and logs, batches of several passes, logs that overflow."""
+tile (32, 64, 128, 256 queries) of every type over splits of several tiles, rows
+that end inside a stage of 64 bytes or a slot of 128, splits whose last tile is
+partial or a single row, k at the edges of its bounds and logs, batches of
+several passes, logs that overflow.  Then the lines between the kernels, and the
+kernels with lists at the shapes they have.  A test that is about one kernel or
+tile asserts that the plan gives its shape to it."""
 import pytest
 import torch
 
@@ -43,7 +46,7 @@ def match(apc, e, es, q, qs, k):
     ws.random_(0, 256)                                   # nothing may depend on what the workspace held
     apc.apc_match_batch(c, q, qs, k, ts, ti, ws)
     torch.cuda.synchronize()
-    assert torch.equal(ts, s1) and torch.equal(ti, i1), "a second pass differs"
+    assert torch.equal(ts.view(torch.int32), s1.view(torch.int32)) and torch.equal(ti, i1), "a second pass differs"
     c.close()
     return ts.double(), ti.long()
 
@@ -98,13 +101,14 @@ def test_tile_buckets_of_several_parts(apc, dtype, b, n, d, k):
 
 @pytest.mark.parametrize("dtype,b,n,d,k", [
     ("f16", 16, 500000, 768, 10), ("f16", 17, 66000, 768, 10), ("bf16", 127, 65536, 768, 9), ("bf16", 128, 65536, 768, 10),
-    ("f16", 256, 65537, 768, 1), ("f16", 256, 65537, 768, 11), ("f16", 257, 65537, 768, 10),      # query-stationary or tiled
+    ("f16", 256, 65537, 768, 1), ("f16", 256, 65537, 768, 11), ("f16", 257, 65537, 768, 10),      # 1536-byte rows
     ("f32", 48, 2000, 256, 5), ("f32", 49, 2000, 256, 5), ("f32", 48, 16384, 256, 5), ("f32", 49, 16384, 256, 5),   # small float32 or tiled
     ("f32", 256, 2400, 64, 32), ("f32", 256, 2401, 64, 32), ("f32", 257, 2000, 128, 9), ("f32", 60, 9600, 192, 1), ("f32", 65, 9600, 192, 1),
-    ("e4m3", 12288, 20001, 512, 7), ("e4m3", 12288, 20000, 512, 7), ("f16", 4097, 20001, 256, 17),  # two wavefronts per SIMD or tiled
+    ("e4m3", 12288, 20001, 512, 7), ("e4m3", 12288, 20000, 512, 7), ("f16", 4097, 20001, 256, 17),
 ])
 def test_routes_meet(apc, dtype, b, n, d, k):
-    """Both sides of every line between the kernels."""
+    """Around lines between the kernels, those of the small float32 kernel among
+    them (the other lines: test_kernels_agree_where_they_meet)."""
     say(f"route {dtype} b={b} n={n} d={d} k={k}")
     e, es = rows(n, d, dtype, n + k)
     q, qs = rows(b, d, dtype, b)
@@ -148,6 +152,102 @@ def test_tile_batches_of_several_passes(apc, b):
     q, _ = rows(b, d, "f32", 4)
     ts, ti = match(apc, e, None, q, None, k)
     check(e, q, k, ts, ti, 1e-5)
+
+
+# (dtype, queries per tile, b, n, d): splits of 3 to 10 tiles, the last one partial
+TILES = [("f32", 64, 257, 30001, 208), ("f32", 128, 1500, 12001, 208), ("f32", 256, 1500, 30001, 640),
+         ("f16", 64, 129, 50001, 208), ("f16", 128, 2049, 9001, 208), ("f16", 256, 2049, 20001, 640),
+         ("bf16", 64, 129, 50001, 640), ("bf16", 128, 2049, 9001, 640), ("bf16", 256, 3000, 50001, 208),
+         ("e4m3", 64, 257, 30001, 208), ("e4m3", 128, 3000, 9001, 208), ("e4m3", 256, 3000, 30001, 640)]
+
+
+def special(e, es, q, qs):
+    """The last 40 entries are copies of the first, the first 40 queries too; query
+    41 is zero, 50 holds a NaN, the last an infinity (e4m3, which has none: a NaN)."""
+    n = e.shape[0]
+    raw = lambda t: t.view(torch.uint8) if t.dtype == torch.float8_e4m3fn else t
+    raw(e)[n - 40:] = raw(e)[:40]
+    raw(q)[:40] = raw(e)[:40]
+    bad = [41, 50, q.shape[0] - 1]
+    if q.dtype == torch.float8_e4m3fn:
+        raw(q)[41], raw(q)[50, 3], raw(q)[-1, -1] = 0, 0x7F, 0xFF
+    else:
+        q[41], q[50, 3], q[-1, -1] = 0, float("nan"), float("inf")
+    if es is not None:
+        es[n - 40:], qs[:40] = es[:40], es[:40]
+    return bad
+
+
+def check_special(e, q, k, ts, ti, bad, tol, every=97):
+    n, b = e.shape[0], q.shape[0]
+    assert (ti[bad] == -1).all() and torch.isnan(ts[bad]).all()
+    first = torch.arange(40, device="cuda")
+    if k >= 2:                                            # equal scores: the lower entry first
+        assert torch.equal(ti[:40, 0], first) and torch.equal(ti[:40, 1], first + n - 40) and torch.equal(ts[:40, 0], ts[:40, 1])
+    else:
+        assert torch.equal(ti[:40, 0], first)
+    r = torch.tensor(sorted((set(range(0, b, max(1, b // every))) | {b - 2, b // 2}) - set(bad)), device="cuda")
+    check(e, q[r], k, ts[r], ti[r], tol)
+
+
+@pytest.mark.parametrize("dtype,bq,b,n,d", TILES)
+def test_every_tile(apc, dtype, bq, b, n, d):
+    for k in (1, 10, 16) if bq == 256 else (7, 40):
+        say(f"tile of {bq} {dtype} b={b} n={n} d={d} k={k}")
+        p = plan(dtype, b, n, d, k)
+        assert p.kernel == TILE and p.bq == bq and p.tiles >= 3 and p.rows % 256
+        e, es = rows(n, d, dtype, n + d)
+        q, qs = rows(b, d, dtype, b + 7)
+        bad = special(e, es, q, qs)
+        ts, ti = match(apc, e, es, q, qs, k)
+        check_special(e, q, k, ts, ti, bad, {"e4m3": 1e-4}.get(dtype, 1e-5))
+
+
+@pytest.mark.parametrize("dtype,bq,b,n,d", TILES)
+def test_every_tile_logs_overflow(apc, dtype, bq, b, n, d):
+    """In every split each row is nearer than those before it, so every pair of
+    every tile after the first passes the bounds: 256 pairs per query, split and
+    tile for logs of 48 or 96, cut again and again between the tiles."""
+    for k in (5, 16) if bq == 256 else (16, 48):
+        say(f"overflow, tile of {bq} {dtype} b={b} n={n} d={d} k={k}")
+        p = plan(dtype, b, n, d, k)
+        assert p.kernel == TILE and p.bq == bq and p.tiles >= 3
+        a, _ = rows(1, d, "f32", 5)
+        z, _ = rows(1, d, "f32", 6)
+        blocks = (n + 31) // 32
+        starts = torch.tensor([blocks * s // p.splits * 32 for s in range(p.splits)], device="cuda")
+        row = torch.arange(n, device="cuda")
+        pos = row - starts[torch.searchsorted(starts, row, right=True) - 1]
+        t = (1.5 - 1.49 * (pos + row / n) / (p.rows + 1))[:, None]
+        e = a + t * z
+        e /= torch.linalg.vector_norm(e, dim=1, keepdim=True)
+        q = a.repeat(b, 1)
+        sc = [None, None]
+        if dtype == "e4m3":
+            e, q, sc = e * 300, q * 300, [torch.ones(n, device="cuda"), torch.ones(b, device="cuda")]
+        e, q = e.to(DT[dtype]).contiguous(), q.to(DT[dtype]).contiguous()
+        ts, ti = match(apc, e, sc[0], q, sc[1], k)
+        assert torch.equal(ti, ti[:1].expand_as(ti)) and torch.equal(ts, ts[:1].expand_as(ts)), "equal queries differ"
+        check(e, q[:2], k, ts[:2], ti[:2], {"e4m3": 1e-4}.get(dtype, 1e-5))
+
+
+@pytest.mark.parametrize("dtype,bq,b,n,d", [("f32", 128, 3001, 6001, 640), ("f32", 256, 3001, 20001, 640), ("f16", 128, 5001, 6001, 640),
+                                            ("bf16", 256, 3001, 20001, 1040), ("e4m3", 128, 9001, 3001, 640), ("e4m3", 256, 9001, 20001, 640)])
+def test_every_tile_in_several_passes(apc, dtype, bq, b, n, d):
+    """The last pass is not full; both sides of every line between passes."""
+    k = 7
+    say(f"passes, tile of {bq} {dtype} b={b} n={n} d={d}")
+    p = plan(dtype, b, n, d, k)
+    assert p.kernel == TILE and p.bq == bq and p.passes >= 2
+    e, es = rows(n, d, dtype, n + d)
+    q, qs = rows(b, d, dtype, b + 7)
+    bad = special(e, es, q, qs)
+    ts, ti = match(apc, e, es, q, qs, k)
+    check_special(e, q, k, ts, ti, bad, {"e4m3": 1e-4}.get(dtype, 1e-5))
+    few = q[-300:].contiguous()                           # one pass: the same lists, bit for bit
+    assert plan(dtype, 300, n, d, k).passes == 1
+    ts1, ti1 = match(apc, e, es, few, None if qs is None else qs[-300:].contiguous(), k)
+    assert torch.equal(ts1[:-1], ts[-300:-1]) and torch.equal(ti1, ti[-300:])
 
 
 @pytest.mark.parametrize("dtype,b,n,k", [("f16", 40, 6000, 10), ("f16", 300, 3000, 32), ("f32", 300, 5000, 64), ("e4m3", 130, 4000, 16)])
@@ -198,18 +298,45 @@ def test_tile_invalid_queries(apc):
     c.close()
 
 
-@pytest.mark.parametrize("dtype,b,n,d,k", [("f16", 200, 70000, 768, 10), ("bf16", 8, 500000, 768, 5),
+@pytest.mark.parametrize("dtype,b,n,d,k", [("f16", 200, 70000, 768, 10), ("bf16", 70, 20000, 768, 5),
                                             ("e4m3", 12288, 20001, 768, 32), ("f16", 4096, 600000, 256, 3)])
 def test_scores_do_not_depend_on_the_kernel(apc, dtype, b, n, d, k):
     """Lists of a batch that another kernel serves, bit for bit those of the
     tiled kernel on some of its queries: the sums run over d in one order."""
     say(f"one order {dtype} b={b} n={n} d={d} k={k}")
+    few = min(b // 2, 100)
+    assert plan(dtype, b, n, d, k).kernel != TILE and plan(dtype, few, n, d, k).kernel == TILE
     e, es = rows(n, d, dtype, 31)
     q, qs = rows(b, d, dtype, 32)
     ts, ti = match(apc, e, es, q, qs, k)
-    few = min(b, 100)
-    if b < 20:                                           # more queries instead: these are served by the query-stationary kernel
-        q, few = torch.cat([q] * 5), 5 * b
-        ts, ti = torch.cat([ts] * 5), torch.cat([ti] * 5)
-    ts2, ti2 = match(apc, e, es, q[:few].contiguous(), None if qs is None else qs[:1].expand(few).contiguous(), k)
+    ts2, ti2 = match(apc, e, es, q[:few].contiguous(), None if qs is None else qs[:few].contiguous(), k)
     assert torch.equal(ts[:few], ts2) and torch.equal(ti[:few], ti2)
+
+
+@pytest.mark.parametrize("k", [1, 16, 17, 32])
+@pytest.mark.parametrize("rb", [512, 768, 1024])
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "e4m3"])
+def test_two_wavefront_kernel(apc, dtype, rb, k):
+    """Every shape that is built, a partial last group of rows and a batch just
+    past a tile of 256 queries."""
+    b, n, d = 12289, 2111, rb // SIZE[dtype]
+    say(f"k_qs8 {dtype} b={b} n={n} d={d} k={k}")
+    assert KERNEL[plan(dtype, b, n, d, k).kernel] == "k_qs8"
+    e, es = rows(n, d, dtype, n + d)
+    q, qs = rows(b, d, dtype, b + 7)
+    bad = special(e, es, q, qs)
+    ts, ti = match(apc, e, es, q, qs, k)
+    check_special(e, q, k, ts, ti, bad, {"e4m3": 1e-4}.get(dtype, 1e-5), every=200)
+
+
+@pytest.mark.parametrize("b,n,k", [(70, 3001, 1), (70, 3001, 3), (300, 17011, 10), (60, 130, 2)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "e4m3"])
+def test_query_stationary_kernel(apc, dtype, b, n, k):
+    d = 1536 // SIZE[dtype]
+    say(f"k_qs {dtype} b={b} n={n} d={d} k={k}")
+    assert KERNEL[plan(dtype, b, n, d, k).kernel] == "k_qs"
+    e, es = rows(n, d, dtype, n + d)
+    q, qs = rows(b, d, dtype, b + 7)
+    bad = special(e, es, q, qs)
+    ts, ti = match(apc, e, es, q, qs, k)
+    check_special(e, q, k, ts, ti, bad, {"e4m3": 1e-4}.get(dtype, 1e-5))

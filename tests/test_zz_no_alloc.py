@@ -35,9 +35,10 @@ def _both(apc, c, q, qs, k):
     return out
 
 
-@pytest.mark.parametrize("dtype,d,n,bs,k", [("e4m3", 768, 60000, (2000, 300), 32),     # two waves per SIMD
-                                            ("f16", 768, 40000, (700, 100), 10),        # query-stationary kernel
-                                            ("f32", 64, 5000, (300, 17), 5)])           # fp32 rows
+@pytest.mark.parametrize("dtype,d,n,bs,k", [("e4m3", 768, 60000, (2000, 300), 32),     # tiled, 768-byte rows
+                                            ("e4m3", 512, 3000, (12288, 300), 16),      # two wavefronts per SIMD, then tiled
+                                            ("f16", 768, 40000, (700, 100), 10),        # query-stationary kernel, then tiled
+                                            ("f32", 64, 5000, (300, 17), 5)])           # tiled, then small float32
 def test_static_workspace_matches_caller_workspace(apc, dtype, d, n, bs, k):
     e, es = make_rows(n, d, dtype, 71, clusters=max(1, n // 60))
     c = apc.apc_build_cache(e, es)
