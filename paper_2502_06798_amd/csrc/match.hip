@@ -252,7 +252,9 @@ MatchPlan plan_tile(int dt, int64_t n, int64_t rb, int32_t b, int32_t k)
     // with 128; 1,024 x 1,000,000 x 640: 1,346 against 1,477); for other batches
     // the padding and the uneven last round decide (600 x 100,000 x 640 f16:
     // 146 us with 256, 124 with 128; 256 x 100,000 x 768: 92 and 85; 300 x
-    // 20,000 x 384 float32: 127 us with 256, 72 with 64).
+    // 20,000 x 384 float32: 127 us with 256, 72 with 64).  800 random shapes, time
+    // over the fastest tile's in the mean: float32 1.011, 16-bit 1.012, e4m3 1.014,
+    // so 16-bit and e4m3 rows share the stage's time.
     static const struct { int bq; float s, s32, e, f; } kinds[4] = {{256, 1.10f, 4.00f, 4.0f, 12.f},
                                                                     {128, 0.60f, 2.05f, 2.0f, 6.f},
                                                                     {64, 0.36f, 1.05f, 1.2f, 3.f},
@@ -267,10 +269,11 @@ MatchPlan plan_tile(int dt, int64_t n, int64_t rb, int32_t b, int32_t k)
         const int64_t passes = (qt * sp + 255) / 256;
         const float rounds = dt == APC_F32 ? (float)tiles / sp : (float)((tiles + sp - 1) / sp);
         // (three or more tiles of 64 queries over a cache beyond the MALL wait for
-        // their rows: with this term 151 x 9,461,309 x 384 f16 takes 2,045 us, 2,731
-        // without; 151 x 2,000,000 x 768 e4m3 438 and 600; 300 x 1,000,000 x 1,024
-        // e4m3 459 and 577)
-        const float far = kd.bq == 64 && qt > 2 && n * rb > (256ll << 20) && dt != APC_F32 ? 0.06f : 0.f;
+        // their rows.  246 random shapes there, time over the fastest tile's, mean and
+        // shapes more than 20% off: 1.064 and 47 without this term, 1.010 and 4 with
+        // half of it, 1.005 and none: 151 x 9,461,309 x 384 f16 2,731 us without,
+        // 2,045; 166 x 2,500,191 x 256 e4m3, k = 1, 373 with half, 252)
+        const float far = kd.bq == 64 && qt > 2 && n * rb > (256ll << 20) && dt != APC_F32 ? 0.12f : 0.f;
         const float t = passes * (rounds * (stages * ((dt == APC_F32 ? kd.s32 : kd.s) + far) + kd.e) + kd.f);
         if (best > 0.f && t >= best) continue;
         best = t;
@@ -323,7 +326,7 @@ bool qs8_ahead(int64_t n, int64_t b, int32_t k)
 //                      0.91 to 0.97 at 8,000 to 16,000; k = 10 1.0 to 1.28
 //   b 65 to 512        k <= 3 0.74 to 1.0 (b > 128: 1.0 to 1.1 from 1,000,000); k = 5 1.05 below 4,000, 0.78 to 0.95, 1.03 from 500,000;
 //                      k = 7 1.1 below 8,000, 0.84 to 0.97; k = 10 1.2 below 8,000, 0.82 to 1.0 from
-//                      65,000 (b > 256: 16,000), 1.0 to 1.1 from 500,000
+//                      65,000 (b > 256: 16,000), 1.0 to 1.1 from 500,000 (e4m3: with b > 350 too)
 //   b > 512            k = 1 0.63 to 0.95; k = 5 0.81 to 0.95 from 2,000; k = 10 1.15 at 1,000, 0.88 to 1.04
 //                      from 8,000 (b > 2,560: 4,000), 1.05 to 1.1 from 130,000 (e4m3: 60,000)
 bool qs_ahead(int dt, int64_t n, int64_t b, int32_t k)
@@ -332,10 +335,12 @@ bool qs_ahead(int dt, int64_t n, int64_t b, int32_t k)
         const int64_t least = k <= 3 ? 0 : k <= 5 ? 2000 : k <= 7 ? 6000 : b >= 2560 ? 4000 : 8192;
         return n >= least && n <= (dt == APC_E4M3 ? 60000 : 131072);
     }
+    if (k >= 8 && dt == APC_E4M3 && b > 350) return false;
     if (k >= 8) return n < 500000 && (b > 256 ? n >= 16000 : b >= 128 && n >= 65536);
     if (k >= 6) return n < 500000 && b > 128 && n >= 12000;
     if (k >= 4) return b > 64 ? n >= 4000 && n < 500000 : n >= 8000 && n <= 16000;
     if (k == 3 && b <= 64) return n <= 16000;
+    if (b <= 8 && n > 32768 && n <= 50000) return false;           // two groups in the longest of 256 splits, one tile
     return b <= 128 || n < 1000000;
 }
 

@@ -29,7 +29,7 @@ def test_other_float32_caches_are_tiled(b, n, d, k):
     ("k_qs", "f16", 446, 136863, 768, 10), ("k_qs", "f16", 50, 197590, 768, 2), ("k_qs", "e4m3", 5065, 6702, 1536, 1), ("k_qs", "bf16", 300, 32000, 768, 10),
     # and these it took as long or less
     ("k_tile", "f16", 12, 130000, 768, 10), ("k_tile", "f16", 600, 500000, 768, 10), ("k_tile", "e4m3", 2048, 260000, 1536, 2), ("k_tile", "e4m3", 600, 9000, 768, 1),
-    ("k_tile", "f16", 6000, 100000, 512, 10), ("k_tile", "bf16", 3000, 6000, 512, 32),
+    ("k_tile", "f16", 6000, 100000, 512, 10), ("k_tile", "bf16", 3000, 6000, 512, 32), ("k_tile", "e4m3", 411, 312831, 1536, 8), ("k_tile", "bf16", 2, 40048, 768, 2),
 ])
 def test_kernel_of_a_shape(kernel, dtype, b, n, d, k):
     assert KERNEL[plan(dtype, b, n, d, k).kernel] == kernel
@@ -50,6 +50,14 @@ def test_few_rows_take_many_queries_per_pass(dtype, b, n, d, k, most):
     """Passes of few queries over few rows leave most of the chip idle."""
     p = plan(dtype, b, n, d, k)
     assert p.kernel == TILE and p.passes <= most and p.qtiles * p.splits >= 64
+
+
+@pytest.mark.parametrize("dtype,b,n,d,k,far", [("e4m3", 166, 2500191, 256, 1, True), ("e4m3", 190, 1896002, 384, 20, True), ("f16", 151, 9461309, 384, 10, True),
+                                               ("bf16", 180, 400000, 640, 10, True), ("f16", 151, 200000, 384, 10, False), ("f16", 60, 9461309, 384, 10, False)])
+def test_tile_over_caches_beyond_the_mall(dtype, b, n, d, k, far):
+    """Three or more tiles of 64 queries wait for their rows there."""
+    p = plan(dtype, b, n, d, k)
+    assert p.kernel == TILE and (p.bq > 64 if far else p.bq == 64), p
 
 
 @pytest.mark.parametrize("dtype,b,n,d,k,passes", [("bf16", 6196, 4000, 1536, 11, 4), ("f16", 4167, 5141, 1536, 2, 3)])
