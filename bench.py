@@ -34,15 +34,13 @@ MALL_BYTES = 256 << 20
 # (profiles/similarity_hbm_bytes_all_workloads_pmc.md).  They hold for the
 # kernel and plan code they were taken on (hashed without comments); any other
 # code reports null.
-TRAFFIC_SOURCES = ("paper_2502_06798_amd/csrc/qs_kernel.h", "paper_2502_06798_amd/csrc/qs.hip",
-                   "paper_2502_06798_amd/csrc/qs_f16.hip", "paper_2502_06798_amd/csrc/qs_bf16.hip",
-                   "paper_2502_06798_amd/csrc/qs_e4m3.hip",
-                   "paper_2502_06798_amd/csrc/qs8_kernel.h",
-                   "paper_2502_06798_amd/csrc/qs8_f16.hip", "paper_2502_06798_amd/csrc/qs8_bf16.hip",
-                   "paper_2502_06798_amd/csrc/qs8_e4m3.hip", "paper_2502_06798_amd/csrc/match.hip")
-TRAFFIC_SHA256 = "0c9372c2c89e4c07"
-TRAFFIC_BYTES = {"b256_n100k_d768_f16": 160786432, "b1024_n1m_d768_bf16": 1573105664,
-                 "b4096_n4m_d512_f16": 13140833280, "b16384_n10m_d768_e4m3": 149277192192}
+TRAFFIC_SOURCES = tuple("paper_2502_06798_amd/csrc/" + f for f in (
+    "match.hip", "qs_common.h", "qs_kernel.h", "qs.hip", "qs_f16.hip", "qs_bf16.hip", "qs_e4m3.hip",
+    "qs8_kernel.h", "qs8_f16.hip", "qs8_bf16.hip", "qs8_e4m3.hip",
+    "tile_kernel.h", "tile.h", "tile.hip", "tile_f16.hip", "tile_bf16.hip", "tile_e4m3.hip"))
+TRAFFIC_SHA256 = "5806287b407b294b"
+TRAFFIC_BYTES = {"b256_n100k_d768_f16": 160792576, "b1024_n1m_d768_bf16": 2133745664,
+                 "b4096_n4m_d512_f16": 13103668224, "b16384_n10m_d768_e4m3": 148576802816}
 
 
 def log(*a):

@@ -169,8 +169,10 @@ apc_status apc_match_workspace(const apc_cache* c, int32_t b, int32_t k, size_t*
  * for each of the b query rows, the k cache entries with the highest cosine
  * similarity of the stored vectors,
  *     s(q, e) = clamp(<q, e> * f_q * f_e, -1, 1),   f = 1 / |row|,
- * accumulated in float32 over all d elements (no split over d, so scores are
- * deterministic), in the order (score desc, entry index asc).
+ * accumulated in float32 over all d elements in a fixed order (so scores are
+ * deterministic), in the order (score desc, entry index asc).  The order of the
+ * sum does not depend on the batch or the cache, except for APC_F32 caches of
+ * at most 16,384 rows, whose last bits may follow the batch's size.
  *
  * q          b x d row-major queries in the cache's type.
  * q_scale    b float32 (APC_E4M3 only, else NULL).

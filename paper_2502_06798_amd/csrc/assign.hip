@@ -402,9 +402,10 @@ __device__ inline void rounds_flow(const Ranks<QPT, NTB>& rk, const uint8_t* lam
 // its rank inside group (j, pos).  Only group (j, j) mixes queries of several
 // levels; pass 2 ranks its members, the others are ranked by their offset in
 // their level's quota.
-// 16,384 queries, 10 levels: rounds 281 us in k_assign_reg (two barriers and a
-// ballot per level for each of 16 chunks in every round), 63 here; the call by
-// plan 61 us with a barrier pair per chunk, 42 now.
+// 16,384 queries, 10 levels: the rounds 281 us as k_assign_reg does them, with
+// several queries per thread (two barriers and a ballot per level for each of 16
+// chunks in every round), 63 here; the call by plan 61 us with a barrier pair
+// per chunk, 42 now.
 enum { PLAN_GIVEN = 0, PLAN_OPTIMAL = 1, PLAN_ROUNDS = 2 };
 template <int QPT, int NTB, int MODE>
 __global__ __launch_bounds__(NTB) void k_assign_plan(const AssignTable targ, const float* __restrict__ top_score,

@@ -9,8 +9,9 @@
 // a register are merged the same way.  All loads of a query go out at once and
 // the chain is (g P / 64 + log2(64 / P)) log2 2P exchanges, where taking the
 // largest head k times over made k dependent rounds (16,384 queries, 8 shards,
-// k = 32: 66 us before, 25 now, bound by the
-// vector work of the exchanges).  Where a list is not strictly falling (a
+// k = 32: 61 us before, 29 now, the latency of the chain: its LDS permutes, two
+// per exchange, take about 7 us of the LDS's time and its vector instructions 9
+// of the SIMDs').  Where a list is not strictly falling (a
 // non-candidate before a candidate, the same entry twice), a score is -0, or
 // two shards hold the same entry, the wavefront takes the heads one by one:
 // lane s owns the head of shard s's list, each round takes the wavefront

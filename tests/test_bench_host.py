@@ -60,3 +60,13 @@ def test_traffic_table_covers_the_bench_workloads():
                                         "b16384_n10m_d768_e4m3"}
     for name, nbytes in bench.TRAFFIC_BYTES.items():
         assert nbytes >= bench.alg_bytes(synth.BY_NAME[name])        # counters read at least the cache once
+
+
+def test_traffic_figures_follow_every_similarity_source():
+    """The sources whose change voids the counters' figures: all of the similarity
+    kernels that the four workloads can run on, and the plans."""
+    import os
+    csrc = os.path.join(bench.ROOT, "paper_2502_06798_amd", "csrc")
+    want = {f for f in os.listdir(csrc) if f.startswith(("qs", "tile", "match")) and f != "tile_f32.hip"}
+    assert {os.path.basename(f) for f in bench.TRAFFIC_SOURCES} == want
+    assert all(os.path.exists(os.path.join(bench.ROOT, f)) for f in bench.TRAFFIC_SOURCES)
