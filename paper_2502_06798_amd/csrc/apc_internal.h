@@ -66,7 +66,7 @@ hipError_t launch_match(const MatchPlan& p, int dt, int64_t n, int32_t d, const 
                         float* top_score, int32_t* top_idx, void* ws, hipStream_t s,
                         hipEvent_t ev_start, hipEvent_t ev_stop);
 
-// query-stationary kernel for 16-bit rows of 1536 bytes (k <= 10): queries in
+// query-stationary kernel for 16-bit and e4m3 rows of 1536 bytes (k <= 10): queries in
 // VGPRs, cache rows through an LDS ring, per-query bounds shared between
 // workgroups.  qs_queries gives the queries per workgroup (0: not built),
 // qs_group_rows the entries per group (the unit a split is made of).
@@ -133,6 +133,8 @@ hipError_t launch_level_histogram(const int32_t* level, int32_t b, int32_t L, in
 struct ShardOffsets {
     int32_t v[APC_MAX_SHARDS];
 };
+// whether g lists of kin entries are merged head by head, not in registers
+bool merge_by_heads(int32_t g, int32_t kin, int32_t k);
 hipError_t launch_merge_shards(const float* scores, const int32_t* idx, int32_t g, int32_t b, int32_t kin,
                                const ShardOffsets& off, int32_t k, float* out_s, int32_t* out_i, hipStream_t s);
 

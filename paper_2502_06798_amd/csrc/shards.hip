@@ -16,7 +16,8 @@
 // two shards hold the same entry, the wavefront takes the heads one by one:
 // lane s owns the head of shard s's list, each round takes the wavefront
 // maximum of the heads' keys, (score desc, global entry asc) packed into 64
-// bits, and the owning lane advances.
+// bits, and the owning lane advances.  Few entries out of many registers take
+// fewer rounds than exchanges: they go to the heads at once (merge_by_heads).
 #include "apc_internal.h"
 
 namespace apc {
@@ -197,19 +198,54 @@ __global__ __launch_bounds__(MS_WAVES * 64) void k_merge_shards(const float* __r
     }
 }
 
+__global__ __launch_bounds__(MS_WAVES * 64) void k_merge_heads(const float* __restrict__ sc,
+                                                               const int32_t* __restrict__ ix, int32_t g,
+                                                               int32_t b, int32_t kin, const ShardOffsets off,
+                                                               int32_t k, float* __restrict__ out_s,
+                                                               int32_t* __restrict__ out_i)
+{
+    const int64_t q = (int64_t)blockIdx.x * MS_WAVES + (threadIdx.x >> 6);
+    if (q >= b) return;                                       // uniform per wavefront
+    merge_heads(sc, ix, g, b, kin, off, k, q, threadIdx.x & 63, out_s, out_i);
+}
+
+// lanes per list in the registers' merge
+int list_lanes(int32_t kin, int32_t k)
+{
+    const int most = kin > k ? kin : k;
+    return most <= 8 ? 8 : most <= 16 ? 16 : most <= 32 ? 32 : 64;
+}
+
 }  // namespace
+
+// A round of the heads' merge takes as long as about six exchanges (four where a
+// list fills the wavefront: its registers also load the most lanes that hold
+// nothing).  Heads and registers in us: 64 shards of 1,024 queries, k = 10, 7.2
+// and 9.7; 16,384 queries, k = 1, 64 shards 13.4 and 24.2, two 4.8 and 7.4; 64
+// shards of 1,024, k = 48, 26 and 56; on the other side of the line 32 shards of
+// 1,024, k = 24, 14.2 and 10.2; 16,384 queries, two shards, k = 10, 21.4 and 6.5.
+bool merge_by_heads(int32_t g, int32_t kin, int32_t k)
+{
+    const int P = list_lanes(kin, k), regs = (g * P + 63) / 64;
+    const int log = __builtin_ctz(P);
+    const int exchanges = (regs - 1 + 6 - log) * (log + 1);
+    return exchanges + 6 > (P == 64 ? 4 : 6) * k;
+}
 
 hipError_t launch_merge_shards(const float* scores, const int32_t* idx, int32_t g, int32_t b, int32_t kin,
                                const ShardOffsets& off, int32_t k, float* out_s, int32_t* out_i, hipStream_t s)
 {
     if (b <= 0) return hipSuccess;
     const unsigned grid = (unsigned)((b + MS_WAVES - 1) / MS_WAVES);
-    const int most = kin > k ? kin : k;
-#define APC_MS(P) k_merge_shards<P><<<grid, MS_WAVES * 64, 0, s>>>(scores, idx, g, b, kin, off, k, out_s, out_i)
-    if (most <= 8) APC_MS(8);
-    else if (most <= 16) APC_MS(16);
-    else if (most <= 32) APC_MS(32);
-    else APC_MS(64);
+#define APC_MS(KERNEL) KERNEL<<<grid, MS_WAVES * 64, 0, s>>>(scores, idx, g, b, kin, off, k, out_s, out_i)
+    if (merge_by_heads(g, kin, k)) APC_MS(k_merge_heads);
+    else
+        switch (list_lanes(kin, k)) {
+        case 8: APC_MS(k_merge_shards<8>); break;
+        case 16: APC_MS(k_merge_shards<16>); break;
+        case 32: APC_MS(k_merge_shards<32>); break;
+        default: APC_MS(k_merge_shards<64>);
+        }
 #undef APC_MS
     return hipGetLastError();
 }

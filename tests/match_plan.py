@@ -47,3 +47,11 @@ def workspace(dtype, b, n, d, k):
     f.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32]
     f.restype = ctypes.c_size_t
     return f(DT[dtype], n, d, b, k)
+
+
+def merge_by_heads(g, kin, k):
+    """Whether shard lists are merged head by head (csrc/shards.hip)."""
+    f = apc.load()._ZN3apc14merge_by_headsEiii
+    f.argtypes = [ctypes.c_int32] * 3
+    f.restype = ctypes.c_bool
+    return f(g, kin, k)

@@ -40,7 +40,11 @@ def _shard_lists(rng, g, b, kin, n_local):
 
 
 @pytest.mark.parametrize("g,b,kin,k", [(1, 5, 10, 10), (2, 300, 10, 10), (8, 1000, 32, 32), (8, 77, 16, 40),
-                                       (64, 130, 4, 64), (3, 4096, 64, 1), (5, 1, 1, 7)])
+                                       (64, 130, 4, 64), (3, 4096, 64, 1), (5, 1, 1, 7),
+                                       # head by head, then in registers of 8, 16, 32 and 64 lanes
+                                       (64, 33, 10, 10), (64, 9, 48, 48), (64, 1030, 1, 1), (33, 70, 3, 2),
+                                       (64, 35, 8, 8), (7, 66, 3, 8), (64, 33, 16, 16), (13, 50, 9, 10), (32, 21, 24, 24),
+                                       (16, 19, 64, 64), (9, 130, 10, 40)])
 def test_merge_shards_bit_exact(apc, orc, g, b, kin, k):
     say(f"merge_shards g={g} b={b} kin={kin} k={k}")
     rng = np.random.default_rng(g * 1000 + b + kin)

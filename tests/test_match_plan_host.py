@@ -4,7 +4,7 @@ import random
 
 import pytest
 
-from tests.match_plan import F32S, KERNEL, SIZE, TILE, plan, workspace
+from tests.match_plan import F32S, KERNEL, SIZE, TILE, merge_by_heads, plan, workspace
 
 
 @pytest.mark.parametrize("b,n,d,k", [(49, 1000, 1536, 5), (100, 1000, 768, 10), (256, 2000, 768, 10), (96, 5000, 384, 10),
@@ -103,3 +103,15 @@ def test_workspace_of_the_shapes_that_fell():
     """127 queries were asked 8.6 times what 128 were, and so on."""
     for dtype, d, n, k, small, large in (("f16", 768, 300000, 5, 127, 128), ("f16", 256, 300000, 10, 2000, 8192), ("f32", 1024, 200000, 5, 256, 257)):
         assert workspace(dtype, small, n, d, k) <= workspace(dtype, large, n, d, k)
+
+
+@pytest.mark.parametrize("g,kin,k", [(64, 10, 10), (64, 48, 48), (64, 1, 1), (2, 1, 1), (64, 16, 3), (8, 64, 1), (64, 24, 24)])
+def test_few_of_many_shards_entries_by_heads(g, kin, k):
+    """The registers' merge takes 1.2 to 7 times as long there."""
+    assert merge_by_heads(g, kin, k)
+
+
+@pytest.mark.parametrize("g,kin,k", [(2, 10, 10), (16, 10, 10), (64, 8, 8), (64, 16, 16), (32, 24, 24), (8, 32, 32),
+                                     (16, 64, 64), (8, 10, 64), (2, 64, 10)])
+def test_other_shard_lists_in_registers(g, kin, k):
+    assert not merge_by_heads(g, kin, k)
