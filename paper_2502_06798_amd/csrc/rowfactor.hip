@@ -107,10 +107,10 @@ __global__ __launch_bounds__(256) void k_row_factors(const uint8_t* __restrict__
 #pragma unroll
             for (int a = 0; a < m && a + m < A; ++a) ss[i][a] += ss[i][a + m];
 #pragma unroll
-        for (int m = G / 2; m >= 1; m >>= 1) {
-            ss[i][0] += __shfl_xor(ss[i][0], m, 64);
-            bad[i] |= (bool)__shfl_xor((int)bad[i], m, 64);
-        }
+        for (int m = G / 2; m >= 1; m >>= 1) ss[i][0] += __shfl_xor(ss[i][0], m, 64);
+        // any lane of the group
+        const uint64_t who = __ballot(bad[i]);
+        bad[i] = (who >> (threadIdx.x % 64 / G * G) & (~0ull >> (64 - G))) != 0;
     }
     if (gl != 0) return;
 #pragma unroll
@@ -146,12 +146,15 @@ void run_row_factors(int64_t n, int64_t row_bytes, const uint8_t* r, const float
     auto grid = [n](int64_t per) { return dim3((unsigned)((n + per - 1) / per)); };
 #define APC_RF(G, RPG, ...) \
     k_row_factors<DT, G, RPG, ##__VA_ARGS__><<<grid(256 / G * RPG), 256, 0, s>>>(r, n, row_bytes, scale, slots, n_slots, f, st, rowflags)
-    // A batch of queries: every row's loads at once.  Wide rows that take little
-    // decoding have loads enough in flight with a wavefront per row (200,000 rows
-    // of 1,024 floats: 127 us, 138 with two rows per 32 lanes; 300,000 of 2,048
-    // bf16 192 and 206), e4m3 rows do not (1,000,000 of 768: 470 us, 125 with two
-    // per 16 lanes)
-    if (n <= 2048 || (DT != APC_E4M3 && row_bytes > (DT == APC_F32 ? 2048 : 3072))) APC_RF(64, 1);
+    // A wavefront per row, every row's loads at once, up to the number of rows where
+    // that is no longer faster: 4,000 rows of 768 f16 3.4 us, 4.5 with two rows per
+    // 16 lanes, 20,000 8.2 and 7.0; 10,000 of 2,048 e4m3 4.6 and 8.1; 8,000 of 256
+    // f16 3.6 and 3.5.  Wide rows that take little decoding have loads enough in
+    // flight so at any number (200,000 rows of 1,024 floats: 127 us, 138 with two
+    // rows per 32 lanes; 300,000 of 2,048 bf16 192 and 206), e4m3 rows do not
+    // (1,000,000 of 768: 470 us, 125 with two per 16 lanes)
+    const bool wide = DT != APC_E4M3 && row_bytes > (DT == APC_F32 ? 2048 : 3072);
+    if (n <= (row_bytes <= 512 ? 6144 : 10240) || wide) APC_RF(64, 1);
     else if (row_bytes <= 16 * 16) APC_RF(16, 2, 1);
     else if (row_bytes <= 2 * 16 * 16) APC_RF(16, 2, 2);
     else if (row_bytes <= 8 * 16 * 16) APC_RF(16, 2);

@@ -94,23 +94,47 @@ def test_row_factors_depend_on_the_row_alone(apc, dtype, d):
     """The same rows in calls of few and of many rows (lanes per row and rows
     per group differ): the same bits."""
     say(f"row factors of parts {dtype} d={d}")
-    n = 6000
+    n = 10241                                            # above every line between the groupings
     e, _ = make_rows(n, d, dtype, 31)
     whole = torch.empty(n, device="cuda")
     apc.apc_row_factors(e, whole)
-    for a, z in ((0, 1), (0, 2048), (1000, 3049), (17, 2066), (3500, 6000)):
+    for a, z in ((0, 1), (0, 2048), (1000, 3049), (17, 2066), (3500, 6000), (4097, 10241), (1, 10241)):
         part = torch.empty(z - a, device="cuda")
         apc.apc_row_factors(e[a:z], part)
         torch.cuda.synchronize()
         assert torch.equal(part, whole[a:z]), f"rows {a}..{z}"
 
 
+@pytest.mark.parametrize("n", [100, 10241])
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 768), ("f16", 128), ("f16", 384), ("bf16", 1024), ("bf16", 1544),
+                                     ("e4m3", 256), ("e4m3", 768), ("e4m3", 4112)])
+def test_row_factors_of_rows_beside_bad_ones(apc, dtype, d, n):
+    """A value that is not finite, in any lane's part of a row, takes that row's
+    factor alone."""
+    say(f"row factors beside bad rows {dtype} d={d} n={n}")
+    e, _ = make_rows(n, d, dtype, 37)
+    bad = torch.zeros(n, dtype=torch.bool, device="cuda")
+    bad[[0, 5, 6, 33, n - 2]] = True
+    cols = torch.tensor([0, d // 2 + 1, d - 1, 17, d // 3], device="cuda")
+    clean = torch.empty(n, device="cuda")
+    apc.apc_row_factors(e, clean)
+    rows = torch.nonzero(bad).flatten()
+    if dtype == "e4m3":
+        e.view(torch.uint8)[rows, cols] = 0x7F           # the code of NaN
+    else:
+        e[rows, cols] = float("inf")
+    f = torch.empty(n, device="cuda")
+    apc.apc_row_factors(e, f)
+    torch.cuda.synchronize()
+    assert torch.equal(torch.isnan(f), bad) and torch.equal(f[~bad], clean[~bad])
+
+
 @pytest.mark.parametrize("dtype,d", [("f16", 768), ("bf16", 384), ("f16", 1024), ("e4m3", 1536)])
 def test_small_shards_equal_whole_cache(apc, dtype, d):
-    """Shards of fewer and more than 2,048 rows, all of which hold much of every
-    top-k: whole cache and shards agree bit for bit, in the scores too."""
+    """A cache whose row factors take another grouping of lanes than its shards'
+    do, all shards holding much of every top-k: whole cache and shards agree bit for bit, in the scores too."""
     say(f"small shards {dtype} d={d}")
-    cuts, b, k = [0, 100, 1100, 3148, 4100, 8000], 200, 20
+    cuts, b, k = [0, 100, 1100, 3148, 6400, 12600], 200, 20
     n = cuts[-1]
     e, es = make_rows(n, d, dtype, 33, clusters=1)
     q, qs = make_rows(b, d, dtype, 34)
