@@ -4,7 +4,8 @@
 // neighbour j (j < k) and a ballot picks the first resident one, i.e. the
 // best, since the lists are ordered best first.  k_level_histogram: one block;
 // the lanes of a wavefront with the same level find each other by a ballot per
-// bit of it, and the first adds their count in LDS.
+// bit of it, and the first adds their count in LDS; of one or two levels each
+// wavefront counts its queries with a ballot per level.
 #include "apc_internal.h"
 
 namespace apc {
@@ -45,7 +46,9 @@ __global__ __launch_bounds__(RB_WAVES * 64) void k_resident_best(const int32_t* 
 
 // values loaded at once by every thread (with one at a time, and a ballot per
 // level in place of one per bit of it, 16,384 queries over 11 levels took 15 us,
-// and the placement with it 217 us: 210 now)
+// and the placement with it 217 us: 210 now).  Where a value has no more levels
+// than bits, a ballot per level is less work: 300,000 queries of one level 40 us,
+// 61 with one per bit and an atomic for every 64, of two 40 and 78.
 constexpr int LH_NT = 1024, LH_U = 8;
 
 __global__ __launch_bounds__(LH_NT) void k_level_histogram(const int32_t* __restrict__ level, int32_t b, int32_t L,
@@ -56,6 +59,8 @@ __global__ __launch_bounds__(LH_NT) void k_level_histogram(const int32_t* __rest
     if (tid <= L) h[tid] = 0;
     __syncthreads();
     const int bits = 32 - __builtin_clz(n);               // of values 0..n - 1, and n: not counted
+    const bool few = n <= 2;
+    int mine = 0;                                         // few: lane l's count of level l
     for (int base = 0; base < b; base += LH_U * LH_NT) {
         int v[LH_U];
 #pragma unroll
@@ -67,6 +72,11 @@ __global__ __launch_bounds__(LH_NT) void k_level_histogram(const int32_t* __rest
         for (int u = 0; u < LH_U; ++u) {
             if (base + u * LH_NT >= b) break;             // uniform
             const int x = v[u] < 0 || v[u] > L ? n : v[u];
+            if (few) {
+                const int c0 = __popcll(__ballot(x == 0)), c1 = __popcll(__ballot(x == 1));
+                mine += lane == 0 ? c0 : c1;
+                continue;
+            }
             uint64_t same = ~0ull;
             for (int i = 0; i < bits; ++i) {
                 const uint64_t m = __ballot((x >> i) & 1);
@@ -75,6 +85,7 @@ __global__ __launch_bounds__(LH_NT) void k_level_histogram(const int32_t* __rest
             if (x < n && lane == __builtin_ctzll(same)) atomicAdd(&h[x], __popcll(same));
         }
     }
+    if (few && lane < n && mine) atomicAdd(&h[lane], mine);
     __syncthreads();
     if (tid <= L) hist[tid] = h[tid];
 }

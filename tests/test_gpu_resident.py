@@ -111,7 +111,7 @@ def test_resident_fallback_end_to_end(apc, orc):
     c.close()
 
 
-@pytest.mark.parametrize("b,L", [(0, 3), (1, 0), (1000, 5), (5000, 32), (16384, 10)])
+@pytest.mark.parametrize("b,L", [(0, 3), (1, 0), (1000, 5), (5000, 32), (16384, 10), (9001, 0), (16385, 1), (63, 1), (70001, 1), (70001, 2)])
 def test_level_histogram_bit_exact(apc, orc, b, L):
     say(f"level_histogram b={b} L={L}")
     rng = np.random.default_rng(b + L)
